@@ -151,3 +151,24 @@ def test_tree_attention_paper_geometry_long_context():
             e = np.max(np.abs(o[x, h] - ref_o[x, 0])) / np.max(np.abs(ref_o[x, 0]))
             assert e <= 2e-2, (x, h, e)
             assert abs(lse[x, h] - ref_l[x, 0]) <= 1e-4 * abs(ref_l[x, 0]), (x, h)
+
+
+@pytest.mark.parametrize("h_q,h_kv,nodes,n_ctx,n_split", [
+    (2, 2, (1,), (0,), 1),                 # one row, the tree's key alone, one range
+    (2, 2, (64, 3), (1, 959), 2),          # 64 rows: one tile of rows per wave
+    (2, 2, (65, 1), (960, 64), 3),         # 65 rows and 17 key tiles: two tiles per wave
+    (4, 2, (33, 64), (1024, 1023), 40),    # more ranges allowed than tiles; ragged last tile
+    (8, 1, (17, 2, 16), (900, 0, 1100), 9),    # 136 rows: the last chunk one row tile
+    (8, 1, (16, 130), (63, 130), 300),     # short contexts keep one row tile per wave
+])
+def test_tree_attention_row_and_range_edges(h_q, h_kv, nodes, n_ctx, n_split):
+    """Edges of the row chunks (16 and 32 rows per wave, 64 and 128 per block), of the key
+    ranges (one range, more allowed than there are tiles) and of the 64-key tiles."""
+    rng = np.random.default_rng(21)
+    parents = [trees.random_tree(rng, n, 9, trees.bmax_uniform(4)) if n > 1 else trees.chain(1) for n in nodes]
+    n_rows = [n + (i % 2) for i, n in enumerate(nodes)]
+    scale = 1.0 / np.sqrt(D)
+    row_off, total, ctx_off, node_off, a = make_case(22, parents, n_rows, list(n_ctx), h_q, h_kv)
+    say(f"[gpu] tree attention edges h_q={h_q} h_kv={h_kv} nodes={nodes} ctx={n_ctx} n_split={n_split}")
+    o, lse = run_gpu(parents, n_rows, node_off, ctx_off, a, h_q, h_kv, n_split, scale)
+    check(parents, row_off, total, ctx_off, a, o, lse, h_q, h_kv, scale)
