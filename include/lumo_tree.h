@@ -73,9 +73,11 @@ typedef enum { LUMO_F32 = 0, LUMO_BF16 = 1 } lumo_dtype;
 /* Verification schedules (Sec. IV-A, IV-C). All produce the same outputs. */
 typedef enum {
     /* Dependent path groups: the tree is cut into disjoint first-child chains; a
-     * chain starts from the pre-tree state (the spine) or from the exported cut
-     * state of its parent; chains are launched level by level (one launch per
-     * dependency level), each node is updated once. Needs a workspace. */
+     * chain starts from the pre-tree state (the spine) or from the cut state of its
+     * parent; each node is updated once. Needs a workspace: trees that would return to
+     * more than four states, and calls with a state dump, are launched level by level
+     * (one launch per dependency level) through the cut states there; other trees run in
+     * one launch that keeps them in registers (the same bits; so do the next two). */
     LUMO_POLICY_PATHS = 0,
     /* The paper's two launches: the spine exports the cut states of its branch
      * nodes; every other root-to-leaf path then runs from its spine cut state,
@@ -173,7 +175,9 @@ typedef struct {
  *   depth, -1 beyond its depth),
  *   vis[N][2] (per node in slot order, node_off[r] + slot: its preorder position and
  *   the position one past its subtree; node a is an ancestor-or-self of node i iff
- *   vis[a][0] <= vis[i][0] < vis[a][1]).
+ *   vis[a][0] <= vis[i][0] < vis[a][1]); then, for the sequential policies, the words of
+ *   the single-launch scan's traversal (library-internal; a plan without them runs level
+ *   by level).
  * Returns LUMO_EDESC for malformed trees, LUMO_ESPACE (with out->n_words set)
  * when blob is NULL or too small, LUMO_EINVAL for bad arguments.
  */

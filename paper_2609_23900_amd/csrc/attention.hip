@@ -80,6 +80,11 @@ __device__ __forceinline__ float rows_sum(float x) {
 
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 w) { return __builtin_bit_cast(bf16x8, w); }
 
+// a node's preorder position and the end of its subtree (4-byte aligned in the blob)
+struct Interval {
+    int x, y;
+};
+
 // position of key t's 16-byte slots: t's low four bits rotated left by one
 __device__ __forceinline__ int swz(int t) { return ((t << 1) & 14) | ((t >> 3) & 1); }
 
@@ -202,7 +207,7 @@ __global__ __launch_bounds__(64 * kAW, 2) void attn_kernel(AttnParams p) {
             }
         } else {
             const int lo = (i - nct) * kAT;
-            const int2* vis = reinterpret_cast<const int2*>(p.blob + p.o_vis) + base;
+            const Interval* vis = reinterpret_cast<const Interval*>(p.blob + p.o_vis) + base;
             int pos[R];
 #pragma unroll
             for (int t = 0; t < R; ++t) pos[t] = vis[slot[t]].x;
@@ -211,7 +216,7 @@ __global__ __launch_bounds__(64 * kAW, 2) void attn_kernel(AttnParams p) {
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const int sl = lo + 16 * tt + 4 * lg + x;
-                    const int2 iv = vis[min(sl, N - 1)];
+                    const Interval iv = vis[min(sl, N - 1)];
 #pragma unroll
                     for (int t = 0; t < R; ++t)
                         if (sl >= N || pos[t] < iv.x || pos[t] >= iv.y) s[t][tt][x] = -INFINITY;

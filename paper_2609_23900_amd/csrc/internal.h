@@ -18,4 +18,17 @@ constexpr int kPreChunk = 32;     // preorder positions per chunk
 constexpr int kPreStack = 16;     // path-stack candidate slots per chunk
 constexpr int kPreCiWords = 4;    // candidate-slot words per preorder position (16 bytes)
 
+// Traversal of the single-launch scan, behind the last named section of the blob of a
+// sequential policy's plan: {slots, mark}, then {row, code} per node. Its offset, or -1 for a
+// plan without it (the WY policy; words written before the section existed).
+constexpr int kScanHead = 2;
+constexpr int kScanWords = 2;
+constexpr int32_t kScanMark = 0x5ca11;
+inline int64_t scan_section(const lumo_plan& p, const int32_t* host_blob) {
+    int64_t at = p.o_vis + 2 * (int64_t)p.total_nodes;
+    at += at & 1;  // 8-byte entries
+    if (p.policy == LUMO_POLICY_WY || at + kScanHead + kScanWords * (int64_t)p.total_nodes > p.n_words) return -1;
+    return host_blob[at + 1] == kScanMark ? at : -1;
+}
+
 }  // namespace lumo

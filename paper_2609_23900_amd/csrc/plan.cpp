@@ -91,6 +91,44 @@ lumo_status build_tree(int r, int n, const int32_t* parent, ReqTree& t) {
     return LUMO_OK;
 }
 
+// One traversal of a tree for the single-launch scan: {row, code} per visited node, code =
+// source | save << 8 with source 0 = the state of the node visited before, 1 = the
+// pre-tree state, 2 + s = saved state s, and save 0 = none, 1 + s = into slot s. A node
+// with several children is saved once and restored for each child but the last; the child
+// whose own subtree needs most slots comes last, so that a tree needs at most
+// log2(leaves) of them (three or four for the random trees of 64 to 256 nodes of the
+// benchmark, one for the evaluated draft geometry). Returns the slots needed.
+int scan_order(const ReqTree& t, int row_base, int32_t* out) {
+    if (!t.n) return 0;
+    std::vector<int> need(t.n, 0), order;
+    auto by_need = [&](int a, int b) { return need[a] != need[b] ? need[a] < need[b] : a < b; };
+    std::vector<int> kids(t.child);  // CSR as child_off, each list ordered by need
+    for (int x = t.n - 1; x >= 0; --x) {
+        int* first = kids.data() + t.child_off[x];
+        const int nc = t.n_children(x);
+        if (nc == 0) continue;
+        std::sort(first, first + nc, by_need);
+        need[x] = nc == 1 ? need[first[0]] : std::max(need[first[nc - 1]], 1 + need[first[nc - 2]]);
+    }
+    struct Visit {
+        int node, source, level;  // level: slots held by ancestors with unvisited children
+    };
+    std::vector<Visit> stack{{0, 1, 0}};
+    while (!stack.empty()) {
+        const Visit v = stack.back();
+        stack.pop_back();
+        const int nc = t.n_children(v.node);
+        const int* first = kids.data() + t.child_off[v.node];
+        *out++ = row_base + t.slot[v.node];
+        *out++ = v.source | (nc > 1 ? v.level + 1 : 0) << 8;
+        // the first child continues from this node's state; the others restore it, the
+        // last of them with the slot free for its own subtree
+        for (int c = nc - 1; c >= 0; --c)
+            stack.push_back({first[c], c == 0 ? 0 : 2 + v.level, c == nc - 1 ? v.level : v.level + 1});
+    }
+    return need[0];
+}
+
 }  // namespace
 
 extern "C" lumo_status lumo_tree_plan(int32_t n_req, const int32_t* node_off, const int32_t* parent,
@@ -277,6 +315,10 @@ extern "C" lumo_status lumo_tree_plan(int32_t n_req, const int32_t* node_off, co
     p.o_chunk_off = take(n_req + 1);
     p.o_chunk_stack = take((int64_t)lumo::kPreStack * p.n_chunks);
     p.o_vis = take(2 * N);
+    // the traversal of the sequential policies' single-launch scan, behind the last named
+    // section (lumo::scan_section)
+    if (policy != LUMO_POLICY_WY) w += w & 1;  // 8-byte entries
+    const int64_t o_scan = policy == LUMO_POLICY_WY ? -1 : take(lumo::kScanHead + lumo::kScanWords * N);
     if (w > (int64_t(1) << 30)) return lumo::fail(LUMO_ESHAPE, "lumo_tree_plan: plan too large");
     p.n_words = (int32_t)w;
     *out = p;
@@ -285,6 +327,7 @@ extern "C" lumo_status lumo_tree_plan(int32_t n_req, const int32_t* node_off, co
 
     // ---- write --------------------------------------------------------------------------
     int32_t* b = blob;
+    if (o_scan > 0) b[o_scan - 1] = 0;  // the alignment word, or the last section's end (written below)
     for (int r = 0; r <= n_req; ++r) {
         b[p.o_node_off + r] = node_off[r];
         b[p.o_row_off + r] = row_base[r];
@@ -389,5 +432,13 @@ extern "C" lumo_status lumo_tree_plan(int32_t n_req, const int32_t* node_off, co
         }
     }
     b[p.o_level_off + p.n_levels] = si;
+    if (o_scan >= 0) {
+        int slots = 0;
+        for (int r = 0; r < n_req; ++r)
+            slots = std::max(slots, scan_order(tr[r], row_base[r],
+                                               b + o_scan + lumo::kScanHead + (int64_t)lumo::kScanWords * node_off[r]));
+        b[o_scan] = slots;
+        b[o_scan + 1] = lumo::kScanMark;
+    }
     return LUMO_OK;
 }

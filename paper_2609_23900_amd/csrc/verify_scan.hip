@@ -1,7 +1,9 @@
 // Path-parallel tree verification by sequential path scans (LumoTree Sec. IV-A,
-// Alg. 2; Eq. (2)-(3)).
+// Alg. 2; Eq. (2)-(3)), in two forms that give the same bits: level by level through cut
+// states in the workspace (scan_kernel), and the whole tree in one launch with the
+// states it returns to in registers (scan_tree_kernel, below).
 //
-// One wavefront per (segment, layer, value head, 64-wide value tile). Each lane owns
+// scan_kernel: one wavefront per (segment, layer, value head, 64-wide value tile). Each lane owns
 // one value row j of the head matrix R (the full key dimension, d_k fp32 values, in
 // VGPRs) and carries it through every node of its segment: the state tile is loaded
 // once (pre-tree state or an exported cut state) and reused across the path loop.
@@ -94,6 +96,253 @@ __global__ __launch_bounds__(64) void scan_kernel(ScanParams p, const typename O
     }
 }
 
+// The same scan in one launch, without cut states in memory. The level-by-level schedules
+// above move every cut state to the workspace and back (a 64-node tree: 19 stores and 37
+// loads of a 64 KB tile per value head; the batched workload 48 GB per call against 1.4 GB
+// of operands and states, at 5 TB/s). Here a wavefront takes 16 value columns through the
+// whole tree, depth first, and keeps the states it returns to in registers: with the
+// child that needs most of them visited last a tree needs at most log2(leaves) saved
+// states (plan.cpp), and a column tile this narrow leaves room for NS of them.
+//
+// Lane 4 c + r holds the keys i = r (mod 4) of column c: element i of a dot product goes
+// into partial sum i % 4 (Dot4), so each lane owns one of the four chains of its column
+// and two quad exchanges add them in Dot4's order. Every value is computed with the
+// operations, and in the order, of scan_kernel, so the outputs are the same bits.
+//
+// A block is four such wavefronts of one key head ((value head, 16-column tile) pairs),
+// which share the key and query rows: chunks of kScanChunk visited nodes, converted to
+// fp32 and split by i % 4 on the way into LDS, one chunk ahead of their use. Bound by the
+// vector ALUs (128 of about 190 instructions per node and wave are the recurrence's fma
+// and mul at d_k = 128) with the LDS port next (the rows are read by every wave).
+constexpr int kScanChunk = 16;
+
+struct ScanTreeParams {
+    const int32_t* blob;
+    int32_t o_node_off, o_order;
+    int32_t n_layers, total_rows, h_k, h_v, d_v, group, n_ct, nwk, n_wb;
+};
+
+// x of the lane whose index differs in bit 0 (quad_perm 1,0,3,2) or 1 (2,3,0,1)
+template <int CTRL> __device__ __forceinline__ float quad_swap(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+// (s0 + s1) + (s2 + s3) of a quad's four partial sums, in all four lanes
+__device__ __forceinline__ float quad_sum(float s) {
+    s = s + quad_swap<0xB1>(s);
+    return s + quad_swap<0x4E>(s);
+}
+
+template <int DK, int OPT, int NS>
+__global__ __launch_bounds__(256, 2) void scan_tree_kernel(ScanTreeParams p,
+                                                           const typename Op<OPT>::T* __restrict__ q,
+                                                           const typename Op<OPT>::T* __restrict__ k,
+                                                           const typename Op<OPT>::T* __restrict__ v,
+                                                           const float* __restrict__ g, const float* __restrict__ gbeta,
+                                                           const float* __restrict__ state0,
+                                                           typename Op<OPT>::T* __restrict__ o) {
+    using T = typename Op<OPT>::T;
+    constexpr int KC = kScanChunk;
+    constexpr int E = DK / 4;    // keys per lane
+    constexpr int RS = E + 4;    // floats per residue row (padded: the four rows on different banks)
+    constexpr int EPT = DK / 16;  // row elements a thread stages (16 threads per node)
+    struct __attribute__((aligned(EPT * sizeof(T)))) Piece {
+        T e[EPT];
+    };
+    __shared__ __attribute__((aligned(16))) float rows[2][KC][2][4 * RS];  // [buffer][node][key, query]
+    __shared__ __attribute__((aligned(16))) float4 heads[2][4][KC];        // per wave: {alpha, beta, row, code}
+    __shared__ __attribute__((aligned(16))) float vals[2][4][KC][16];      // per wave: values, then outputs
+    const int tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+
+    // the blocks of a (request, layer) on one XCD (shared rows), the units over all of them
+    int blk = xcd_units(blockIdx.x, gridDim.x, p.h_k * p.n_wb);
+    const int wb = blk % p.n_wb;
+    blk /= p.n_wb;
+    const int hk = blk % p.h_k;
+    blk /= p.h_k;
+    const int l = blk % p.n_layers;
+    const int r = blk / p.n_layers;
+    const int base = p.blob[p.o_node_off + r];
+    const int N = p.blob[p.o_node_off + r + 1] - base;
+    if (N <= 0) return;  // uniform over the block
+    const int gw = wb * 4 + wave;
+    const bool wact = gw < p.nwk;  // uniform: idle waves stage rows only
+    const int h = hk * p.group + (wact ? gw / p.n_ct : 0);
+    const int j0 = (wact ? gw % p.n_ct : 0) * 16;
+    const int c = lane >> 2, res = lane & 3;
+    const int2* order = reinterpret_cast<const int2*>(p.blob + p.o_order) + base;
+    const long lrow = (long)l * p.total_rows;
+
+    float S[E];
+    {
+        const float* S0 = state0 + (((long)r * p.n_layers + l) * p.h_v + h) * (long)DK * p.d_v + (long)res * p.d_v + j0 + c;
+#pragma unroll
+        for (int t = 0; t < E; ++t) S[t] = S0[(long)(4 * t) * p.d_v];
+    }
+    float saved[NS][E];
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+#pragma unroll
+        for (int t = 0; t < E; ++t) saved[s][t] = 0.f;
+
+    // Staging of the chunk at c0: thread tid carries elements EPT (tid % 16) .. of node
+    // tid / 16's key and query rows; lane (n = lane / 4, columns 4 (lane % 4) ..) its
+    // wave's values of node n and, once per node, gates and code. Positions past the end
+    // repeat the last node (staged, never visited).
+    struct Regs {
+        Piece kp, qp;
+        T vv[4];
+        float gv, bv;
+        int2 en;
+    };
+    const int sn = tid >> 4, sp = tid & 15;
+    auto fetch = [&](int2 block_en, int2 wave_en, Regs& x) {
+        const long kr = ((lrow + block_en.x) * p.h_k + hk) * DK + EPT * sp;
+        x.kp = *reinterpret_cast<const Piece*>(k + kr);
+        x.qp = *reinterpret_cast<const Piece*>(q + kr);
+        const long gi = (lrow + wave_en.x) * p.h_v + h;
+        x.gv = g[gi];
+        x.bv = gbeta[gi];
+        struct __attribute__((aligned(4 * sizeof(T)))) V4 {
+            T e[4];
+        };
+        const V4 w = *reinterpret_cast<const V4*>(v + gi * p.d_v + j0 + 4 * res);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x.vv[e] = w.e[e];
+        x.en = wave_en;
+    };
+    auto store = [&](const Regs& x, int buf) {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int i = EPT * sp + e;
+            rows[buf][sn][0][(i & 3) * RS + (i >> 2)] = Op<OPT>::ld(x.kp.e, e);
+            rows[buf][sn][1][(i & 3) * RS + (i >> 2)] = Op<OPT>::ld(x.qp.e, e);
+        }
+        *reinterpret_cast<float4*>(&vals[buf][wave][c][4 * res]) =
+            make_float4(Op<OPT>::ld(x.vv, 0), Op<OPT>::ld(x.vv, 1), Op<OPT>::ld(x.vv, 2), Op<OPT>::ld(x.vv, 3));
+        if (res == 0)
+            heads[buf][wave][c] = make_float4(__expf(x.gv), x.bv, __int_as_float(x.en.x), __int_as_float(x.en.y));
+    };
+    auto entry = [&](int pos) { return order[min(pos, N - 1)]; };
+
+    Regs nx;
+    fetch(entry(sn), entry(c), nx);
+    store(nx, 0);
+    int2 ebn = entry(KC + sn), ewn = entry(KC + c);
+    __syncthreads();
+    for (int c0 = 0, buf = 0; c0 < N; c0 += KC, buf ^= 1) {
+        const bool more = c0 + KC < N;
+        if (more) {
+            fetch(ebn, ewn, nx);
+            ebn = entry(c0 + 2 * KC + sn);
+            ewn = entry(c0 + 2 * KC + c);
+        }
+        const int cnt = min(N - c0, KC);
+        if (wact) {
+            for (int n = 0; n < cnt; ++n) {
+                const float4 hd = heads[buf][wave][n];
+                const int code = __builtin_amdgcn_readfirstlane(__float_as_int(hd.w));
+                const float alpha = hd.x, beta = hd.y;
+                const float vj = vals[buf][wave][n][c];
+                const float* kr = &rows[buf][n][0][res * RS];
+                const float* qr = &rows[buf][n][1][res * RS];
+                const int src = code & 0xff, save = code >> 8;  // uniform
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    if (src == 2 + s) {
+#pragma unroll
+                        for (int t = 0; t < E; ++t) S[t] = saved[s][t];
+                    }
+                float kf[E];
+#pragma unroll
+                for (int t = 0; t < E; t += 4) {
+                    const float4 w = *reinterpret_cast<const float4*>(kr + t);
+                    kf[t] = w.x;
+                    kf[t + 1] = w.y;
+                    kf[t + 2] = w.z;
+                    kf[t + 3] = w.w;
+                }
+                float u = 0.f;
+#pragma unroll
+                for (int t = 0; t < E; ++t) u = __builtin_fmaf(S[t], kf[t], u);
+                u = quad_sum(u);
+                const float delta = beta * __builtin_fmaf(-alpha, u, vj);
+                float ov = 0.f;
+#pragma unroll
+                for (int t = 0; t < E; t += 4) {
+                    const float4 w = *reinterpret_cast<const float4*>(qr + t);
+                    S[t] = __builtin_fmaf(delta, kf[t], alpha * S[t]);
+                    S[t + 1] = __builtin_fmaf(delta, kf[t + 1], alpha * S[t + 1]);
+                    S[t + 2] = __builtin_fmaf(delta, kf[t + 2], alpha * S[t + 2]);
+                    S[t + 3] = __builtin_fmaf(delta, kf[t + 3], alpha * S[t + 3]);
+                    ov = __builtin_fmaf(S[t], w.x, ov);
+                    ov = __builtin_fmaf(S[t + 1], w.y, ov);
+                    ov = __builtin_fmaf(S[t + 2], w.z, ov);
+                    ov = __builtin_fmaf(S[t + 3], w.w, ov);
+                }
+                ov = quad_sum(ov);
+                vals[buf][wave][n][c] = ov;  // the quad's four lanes write the same value
+#pragma unroll
+                for (int s = 0; s < NS; ++s)
+                    if (save == 1 + s) {
+#pragma unroll
+                        for (int t = 0; t < E; ++t) saved[s][t] = S[t];
+                    }
+            }
+            // the chunk's outputs of this wave: node lane / 4, columns 4 (lane % 4) ..
+            if (c < cnt) {
+                const float4 w = *reinterpret_cast<const float4*>(&vals[buf][wave][c][4 * res]);
+                const int row = __float_as_int(heads[buf][wave][c].z);
+                T* dst = o + ((lrow + row) * p.h_v + h) * p.d_v + j0 + 4 * res;
+                if constexpr (OPT == 1)
+                    *reinterpret_cast<uint2*>(dst) = make_uint2(f32x2_to_bf16x2(w.x, w.y), f32x2_to_bf16x2(w.z, w.w));
+                else
+                    *reinterpret_cast<float4*>(dst) = w;
+            }
+        }
+        if (more) store(nx, buf ^ 1);  // its last readers passed the previous barrier
+        __syncthreads();
+    }
+}
+
+template <int DK, int OPT, int NS>
+hipError_t launch_tree_ns(const ScanTreeParams& p, long nb, hipStream_t s, const GdnArgs& a) {
+    using T = typename Op<OPT>::T;
+    hipLaunchKernelGGL((scan_tree_kernel<DK, OPT, NS>), dim3((unsigned)nb), dim3(256), 0, s, p, static_cast<const T*>(a.q),
+                       static_cast<const T*>(a.k), static_cast<const T*>(a.v), a.g, a.beta, a.state0,
+                       static_cast<T*>(a.o));
+    return hipGetLastError();
+}
+
+constexpr int kScanSlots = 4;  // most saved states (registers) of scan_tree_kernel
+
+template <int OPT>
+hipError_t launch_tree(int dk, const ScanTreeParams& p, long nb, hipStream_t s, const GdnArgs& a) {
+    switch (dk) {
+        case 16: return launch_tree_ns<16, OPT, kScanSlots>(p, nb, s, a);
+        case 32: return launch_tree_ns<32, OPT, kScanSlots>(p, nb, s, a);
+        case 64: return launch_tree_ns<64, OPT, kScanSlots>(p, nb, s, a);
+        default: return launch_tree_ns<128, OPT, kScanSlots>(p, nb, s, a);
+    }
+}
+
+// Whether scan_tree_kernel takes a call: plans that carry the traversal and need at most
+// kScanSlots saved states, without node-state dump or operand preparation. It is the faster
+// form of PATHS and TWO_LEVEL at every size measured (8 requests x 6 layers x 64 nodes,
+// 32 heads, d = 128: 1,175 -> 280 us; one request, one layer, 64 nodes: 83 -> 38 us).
+// RECOMPUTE runs every root-to-leaf path side by side, so a call too small to fill the
+// device takes the depth of its trees (about 3.3 us a level) instead of their nodes
+// (0.55 us each): one request, one layer, 64 nodes of 8 levels 26.7 us against 37.5 us; with
+// 1,024 column tiles (4 requests of 150 nodes) it is 209 us against 95 us.
+bool scan_tree_takes(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, int64_t section) {
+    const lumo_plan& pl = desc.plan;
+    if (section < 0 || desc.host_blob[section] > kScanSlots || a.node_states || a.prep.flags != 0) return false;
+    if (pl.policy != LUMO_POLICY_RECOMPUTE) return true;
+    const long tiles = (long)d.n_req * d.n_layers * d.h_v * (d.d_v / 16);
+    return tiles > 256 || pl.max_nodes <= 6 * pl.max_depth;
+}
+
 template <int DK, int OPT>
 void launch_one(dim3 grid, hipStream_t s, const ScanParams& p, const GdnArgs& a) {
     using T = typename Op<OPT>::T;
@@ -117,6 +366,24 @@ hipError_t launch_dk(int dk, dim3 grid, hipStream_t s, const ScanParams& p, cons
 
 hipError_t launch_scan(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s) {
     const lumo_plan& pl = desc.plan;
+    const int64_t section = scan_section(pl, desc.host_blob);
+    if (scan_tree_takes(d, desc, a, section)) {
+        ScanTreeParams p;
+        p.blob = desc.blob;
+        p.o_node_off = pl.o_node_off;
+        p.o_order = (int32_t)section + kScanHead;
+        p.n_layers = d.n_layers;
+        p.total_rows = pl.total_rows;
+        p.h_k = d.h_k;
+        p.h_v = d.h_v;
+        p.d_v = d.d_v;
+        p.group = d.h_v / d.h_k;
+        p.n_ct = d.d_v / 16;
+        p.nwk = p.group * p.n_ct;
+        p.n_wb = (p.nwk + 3) / 4;
+        const long nb = (long)d.n_req * d.n_layers * d.h_k * p.n_wb;
+        return d.op_dtype == LUMO_BF16 ? launch_tree<1>(d.d_k, p, nb, s, a) : launch_tree<0>(d.d_k, p, nb, s, a);
+    }
     ScanParams p;
     p.blob = desc.blob;
     p.o_seg = pl.o_seg;

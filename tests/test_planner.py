@@ -224,3 +224,46 @@ def test_visibility_intervals_match_ancestry():
             for a in range(len(par)):
                 lo, hi = vis[base + slot[a]]
                 assert (lo <= vis[base + slot[i]][0] < hi) == (a in anc), (r, a, i)
+
+
+@pytest.mark.parametrize("policy", [L.LUMO_POLICY_PATHS, L.LUMO_POLICY_TWO_LEVEL, L.LUMO_POLICY_RECOMPUTE])
+def test_scan_traversal_words(policy):
+    """The single-launch scan's traversal (behind the visibility section, 8-byte aligned):
+    every node visited once, from exactly its parent's state, with at most log2(leaves)
+    saved states; the WY plan carries none."""
+    rng = np.random.default_rng(17)
+    parents = [_tree_of(rng, n) for n in (1, 2, 7, 64, 0, 33, 255, 900)]
+    parents += [np.arange(-1, 39, dtype=np.int32), np.array([-1] + [0] * 40, np.int32)]
+    n_rows = np.array([len(p) + i % 3 for i, p in enumerate(parents)], np.int32)
+    node_off = np.concatenate([[0], np.cumsum([len(p) for p in parents])]).astype(np.int32)
+    plan, blob = L.lumo_tree_plan(node_off, np.concatenate(parents), n_rows, policy)
+    N = plan.total_nodes
+    at = plan.o_vis + 2 * N
+    at += at % 2
+    assert plan.n_words == at + 2 + 2 * N
+    wy, _ = L.lumo_tree_plan(node_off, np.concatenate(parents), n_rows, L.LUMO_POLICY_WY)
+    assert wy.n_words == wy.o_vis + 2 * N
+    words = blob[at + 2:].reshape(-1, 2)
+    rows = blob[plan.o_row:plan.o_row + N]
+    most = 0
+    for r, par in enumerate(parents):
+        lo = int(node_off[r])
+        node_of = {int(rows[lo + i]): i for i in range(len(par))}
+        saved, last, seen = {}, None, set()
+        for row, code in words[lo:lo + len(par)]:
+            node, source, save = node_of[int(row)], int(code) & 0xff, int(code) >> 8
+            state = {0: last, 1: -1}.get(source, saved.get(source - 2))
+            assert state == int(par[node]), (r, node)
+            seen.add(node)
+            last = node
+            if save:
+                saved[save - 1] = node
+        assert len(seen) == len(par)
+        leaves = len(set(range(len(par))) - set(int(p) for p in par))
+        assert len(saved) <= max(0, leaves.bit_length() - 1)
+        most = max(most, len(saved))
+    assert blob[at] >= most
+
+
+def _tree_of(rng, n):
+    return np.array([-1] + [int(rng.integers(0, i)) for i in range(1, n)][:max(n - 1, 0)], np.int32)[:n]
