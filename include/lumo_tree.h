@@ -87,11 +87,11 @@ typedef enum {
      * states, shared prefixes recomputed. No workspace. */
     LUMO_POLICY_RECOMPUTE = 2,
     /* Tree WY form: R_t = gamma_t R0 + sum over ancestors of decayed rank-1
-     * terms. With bf16 operands, d_k = d_v = 128 and paths of at most 17 nodes the
-     * R0 [K | Q] products run on MFMA (R0 as bf16 hi + lo) and the ancestor-masked
-     * triangular system on the vector units; other shapes (fp32 operands, d_k in
-     * {16, 32, 64}, d_v below 128, paths of 18 to 32 nodes) run the same form on the
-     * vector units in fp32. Paths longer than 32 nodes are refused
+     * terms. With bf16 operands and d_k = d_v = 128 the R0 [K | Q] products run on MFMA
+     * (R0 as bf16 hi + lo; with paths of 18 to 32 nodes as three parts, exactly) and the
+     * ancestor-masked triangular system on the vector units; other shapes (fp32
+     * operands, d_k in {16, 32, 64}, d_v below 128) run the same form on the vector
+     * units in fp32. Paths longer than 32 nodes are refused
      * (LUMO_EUNSUPPORTED). One launch, no workspace, no state dump. Outputs agree
      * with the sequential schedules to rounding, not bitwise. */
     LUMO_POLICY_WY = 3

@@ -83,14 +83,14 @@ lumo_status check_wy_verify(const lumo_gdn_dims* d, const lumo_tree_desc* desc, 
     if (desc->plan.policy != LUMO_POLICY_WY)
         return fail(LUMO_EUNSUPPORTED, "%s: needs a plan built for LUMO_POLICY_WY (plan policy %d)", fn,
                     desc->plan.policy);
-    if (!wy_mfma_shape(*d, desc->plan) && desc->plan.max_depth > kWyvMaxDepth)
+    if (!wy_mfma_shape(*d, *desc) && desc->plan.max_depth > kWyvMaxDepth)
         return fail(LUMO_EUNSUPPORTED, "%s: the WY policy handles paths of at most %d nodes (plan has %d)", fn,
                     kWyvMaxDepth, desc->plan.max_depth);
     return LUMO_OK;
 }
 
 hipError_t launch_wy_any(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s) {
-    return wy_mfma_shape(d, desc.plan) ? launch_wy(d, desc, a, s) : launch_wyv(d, desc, a, s);
+    return wy_mfma_shape(d, desc) ? launch_wy(d, desc, a, s) : launch_wyv(d, desc, a, s);
 }
 
 // Operand preparation: flags, constant and gate parameters; NULL means none.

@@ -317,6 +317,7 @@ extern "C" lumo_status lumo_tree_plan(int32_t n_req, const int32_t* node_off, co
     p.o_vis = take(2 * N);
     // the traversal of the sequential policies' single-launch scan, behind the last named
     // section (lumo::scan_section)
+    const int64_t o_deep = lumo::deep_plan(p) ? take(lumo::deep_words(p)) : -1;  // lumo::deep_section
     if (policy != LUMO_POLICY_WY) w += w & 1;  // 8-byte entries
     const int64_t o_scan = policy == LUMO_POLICY_WY ? -1 : take(lumo::kScanHead + lumo::kScanWords * N);
     if (w > (int64_t(1) << 30)) return lumo::fail(LUMO_ESHAPE, "lumo_tree_plan: plan too large");
@@ -394,20 +395,26 @@ extern "C" lumo_status lumo_tree_plan(int32_t n_req, const int32_t* node_off, co
             b[p.o_pre_depth + base + pos] = t.depth[x];
             anc.assign(t.depth[x], 0);
             for (int y = t.parent[x], m = t.depth[x] - 1; y >= 0; y = t.parent[y], --m) anc[m] = y;
-            uint32_t ci[lumo::kPreCiWords] = {};
-            for (int m = 0; m < 4 * lumo::kPreCiWords; ++m) {
-                uint32_t slot = 0xffu;  // no ancestor at this depth (or deeper than the table)
-                if (m < t.depth[x]) {
+            // candidate slots with `cap` stack slots: byte m for the ancestor at depth m
+            auto slots = [&](int cap, int32_t* out) {
+                unsigned char* byte = reinterpret_cast<unsigned char*>(out);  // little-endian words
+                std::memset(byte, 0xff, cap);  // no ancestor at this depth (or deeper than the table)
+                for (int m = 0; m < cap && m < t.depth[x]; ++m) {
                     const int ap = t.dfs_pos[anc[m]];
-                    slot = ap >= c0 ? (uint32_t)(lumo::kPreStack + (ap - c0)) : (uint32_t)m;
+                    byte[m] = (unsigned char)(ap >= c0 ? cap + (ap - c0) : m);
                 }
-                ci[m / 4] |= slot << (8 * (m % 4));
-            }
-            for (int w = 0; w < lumo::kPreCiWords; ++w) b[p.o_pre_ci + (int64_t)lumo::kPreCiWords * (base + pos) + w] = (int32_t)ci[w];
-            if (pos == c0) {  // chunk start: the path stack is the first node's ancestry
-                int32_t* cs = b + p.o_chunk_stack + (int64_t)lumo::kPreStack * nc;
-                for (int m = 0; m < lumo::kPreStack; ++m)
-                    cs[m] = m < t.depth[x] ? row_base[r] + t.slot[anc[m]] : -1;
+            };
+            // a chunk's path stack is the ancestry of its first node
+            auto stack = [&](int cap, int32_t* out) {
+                for (int m = 0; m < cap; ++m) out[m] = m < t.depth[x] ? row_base[r] + t.slot[anc[m]] : -1;
+            };
+            slots(lumo::kPreStack, b + p.o_pre_ci + (int64_t)lumo::kPreCiWords * (base + pos));
+            int32_t* deep_ci = o_deep >= 0 ? b + o_deep + lumo::kDeepHead : nullptr;
+            if (o_deep >= 0) slots(lumo::kDeepStack, deep_ci + (int64_t)(lumo::kDeepStack / 4) * (base + pos));
+            if (pos == c0) {
+                stack(lumo::kPreStack, b + p.o_chunk_stack + (int64_t)lumo::kPreStack * nc);
+                if (o_deep >= 0)
+                    stack(lumo::kDeepStack, deep_ci + (int64_t)(lumo::kDeepStack / 4) * N + (int64_t)lumo::kDeepStack * nc);
                 ++nc;
             }
         }
@@ -432,6 +439,10 @@ extern "C" lumo_status lumo_tree_plan(int32_t n_req, const int32_t* node_off, co
         }
     }
     b[p.o_level_off + p.n_levels] = si;
+    if (o_deep >= 0) {
+        b[o_deep] = lumo::kDeepMark;
+        b[o_deep + 1] = 0;
+    }
     if (o_scan >= 0) {
         int slots = 0;
         for (int r = 0; r < n_req; ++r)

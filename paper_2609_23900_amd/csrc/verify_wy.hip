@@ -64,8 +64,9 @@ typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int kD = 128;                // d_k = d_v
 constexpr int kTile = kPreChunk;       // nodes per chunk = MFMA tile rows
-constexpr int kStack = kPreStack;      // path-stack candidate slots (depth index < 16)
-constexpr int kCand = kStack + kTile;  // Gram rows: stack slots, then the chunk's nodes
+// path-stack candidate slots of the instance with D path registers (Gram rows: stack slots,
+// then the chunk's nodes)
+template <int D> constexpr int kStackOf = D > kPreStack ? kDeepStack : kPreStack;
 constexpr int kGS = 2 * kTile + 1;     // Gram row stride in floats: [chunk keys | chunk queries], padded
 static_assert(kTile == 32, "one MFMA tile of nodes per chunk");
 
@@ -109,12 +110,11 @@ struct ConvFuseParams {
     int32_t channels, act;
 };
 
-// Block-shared staging of one chunk: [key 32 | query 32 | path-stack key 16] rows of
+// Block-shared staging of one chunk: [key 32 | query 32 | path-stack key] rows of
 // 16 slots of 8 bf16; key block kb of row n sits in slot kb ^ (n & 15), so the
 // fragment reads of a half-wave (32 rows, one key block) spread over all banks.
-constexpr int kTileRows = 2 * kTile + kStack;
-struct KQTile {
-    uint4 slot[kTileRows * 16];
+template <int ROWS> struct KQTile {
+    uint4 slot[ROWS * 16];
 };
 
 // Per-lane view of one chunk. Lanes 0..31 and 32..63 both describe node t = lane % 32
@@ -247,6 +247,23 @@ hipError_t launch_wy_d(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const
                : launch_wy_kernel<D, 1, PEND, false, false, 32>(d, p, a, s, pp);
 }
 
+// Paths of 18 to 32 nodes: the 32-column form with 32 path registers (a 64-column wave's
+// state fragments leave no room for them) over the plan's deep tables. These shapes ran on
+// the vector ALUs with R0 in fp32 before, one node per barrier round: 16 requests x 4
+// layers x 96 nodes x 32 heads 687 us, here 185 us. R0 keeps all its bits: each register is
+// split into three bf16 parts where it is used (hi + mid + lo = x; with two parts, 16
+// bits, the call takes 176 us), and the error against 64-bit arithmetic is what it was.
+// Bound by the per-chunk recursion (VALU issue at two waves per SIMD).
+hipError_t launch_wy_deep(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s,
+                          int64_t section) {
+    WyParams p = wy_params(d, desc, a);
+    p.o_pre_ci = (int32_t)section + kDeepHead;
+    p.o_chunk_stack = p.o_pre_ci + kDeepStack / 4 * desc.plan.total_nodes;
+    const PendParams none{};
+    return (a.prep.flags & LUMO_PREP_QK_NORM) ? launch_wy_kernel<32, 1, false, true, false, 32>(d, p, a, s, none)
+                                              : launch_wy_kernel<32, 1, false, false, false, 32>(d, p, a, s, none);
+}
+
 }  // namespace
 
 PendParams pend_params(const PendArgs& pend) {
@@ -269,7 +286,11 @@ PendParams pend_params(const PendArgs& pend) {
 
 hipError_t launch_wy(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s,
                      const PendArgs* pend) {
-    if (desc.plan.max_depth > kStack + 1) return hipErrorNotSupported;
+    if (desc.plan.max_depth > kWyMaxDepth) {
+        const int64_t section = deep_section(desc.plan, desc.host_blob);
+        if (pend || section < 0) return hipErrorNotSupported;
+        return desc.plan.total_nodes == 0 ? hipSuccess : launch_wy_deep(d, desc, a, s, section);
+    }
     // path-stack registers: depths 0..7 suffice when no path is longer than 9 nodes
     const bool d8 = desc.plan.max_depth <= 9;
     if (!pend) {
@@ -284,7 +305,7 @@ hipError_t launch_wy(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const G
 
 hipError_t launch_wy_conv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s,
                           const PendArgs& pend, const ConvFuseArgs& c) {
-    if (desc.plan.max_depth > kStack + 1 || d.h_v != 2 * d.h_k) return hipErrorNotSupported;
+    if (desc.plan.max_depth > kWyMaxDepth || d.h_v != 2 * d.h_k) return hipErrorNotSupported;
     if (d.n_req == 0) return hipSuccess;
     const bool d8 = desc.plan.max_depth <= 9;
     const WyParams p = wy_params(d, desc, a);
@@ -308,7 +329,7 @@ hipError_t launch_wy_conv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, co
 hipError_t launch_wy_pair(const lumo_gdn_dims& da, const lumo_tree_desc& desca, const GdnArgs& aa, const PendArgs& pa,
                           const lumo_gdn_dims& db, const lumo_tree_desc& descb, const GdnArgs& ab, const PendArgs& pb,
                           hipStream_t s) {
-    if (desca.plan.max_depth > kStack + 1 || descb.plan.max_depth > kStack + 1) return hipErrorNotSupported;
+    if (desca.plan.max_depth > kWyMaxDepth || descb.plan.max_depth > kWyMaxDepth) return hipErrorNotSupported;
     const bool qkn = (aa.prep.flags & LUMO_PREP_QK_NORM) != 0;
     if (qkn != ((ab.prep.flags & LUMO_PREP_QK_NORM) != 0)) return hipErrorNotSupported;
     const bool d8 = desca.plan.max_depth <= 9 && descb.plan.max_depth <= 9;

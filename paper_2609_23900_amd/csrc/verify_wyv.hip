@@ -1,6 +1,6 @@
 // Tree verification in WY form on the vector ALUs: the shapes the matrix-core kernel
-// (verify_wy.hip) does not take -- fp32 operands, d_k or d_v below 128, and paths of up
-// to kWyvMaxDepth nodes -- with the same arithmetic form and no cut states.
+// (verify_wy.hip) does not take -- fp32 operands, d_k or d_v below 128, paths of up to
+// kWyvMaxDepth nodes -- with the same arithmetic form and no cut states.
 //
 // Unrolling Eq. (2)-(3) along a node's ancestry a_0 (root) .. a_{d-1}, t:
 //     R_t = gamma_t R0 + sum_{s ancestor-or-self of t} Gamma(s->t) delta_s k_s^T

@@ -267,3 +267,33 @@ def test_scan_traversal_words(policy):
 
 def _tree_of(rng, n):
     return np.array([-1] + [int(rng.integers(0, i)) for i in range(1, n)][:max(n - 1, 0)], np.int32)[:n]
+
+
+def test_deep_preorder_tables():
+    """WY plans with paths of 18 to 32 nodes carry candidate slots and path stacks of 32
+    depths behind the last section; other plans do not."""
+    rng = np.random.default_rng(23)
+    parents = [trees.chain(32), trees.random_tree(rng, 90, 27, trees.bmax_uniform(2)), np.zeros(0, np.int32),
+               trees.chain(1), trees.random_tree(rng, 65, 20, trees.bmax_uniform(3))]
+    n_rows = np.array([len(p) + 1 for p in parents], np.int32)
+    node_off = np.concatenate([[0], np.cumsum([len(p) for p in parents])]).astype(np.int32)
+    plan, blob = L.lumo_tree_plan(node_off, np.concatenate(parents), n_rows, L.LUMO_POLICY_WY)
+    N, at = plan.total_nodes, plan.o_vis + 2 * plan.total_nodes
+    assert plan.n_words == at + 2 + 8 * N + 32 * plan.n_chunks
+    ci = blob[at + 2:at + 2 + 8 * N].astype(np.uint32).view(np.uint8).reshape(N, 32)
+    stacks = blob[at + 2 + 8 * N:].reshape(-1, 32)
+    chunk = 0
+    row_off = np.concatenate([[0], np.cumsum(n_rows)])
+    for r, par in enumerate(parents):
+        lo, rows = int(node_off[r]), oplan.rows_of(par, int(row_off[r]))
+        dfs = list(blob[plan.o_dfs + lo:plan.o_dfs + lo + len(par)])
+        for pos, x in enumerate(dfs):
+            anc, c0 = oplan.ancestry(par, x)[:-1], pos - pos % 32
+            want = [32 + dfs.index(a) - c0 if dfs.index(a) >= c0 else m for m, a in enumerate(anc)]
+            assert list(ci[lo + pos]) == want + [0xff] * (32 - len(anc))
+            if pos == c0:
+                assert list(stacks[chunk]) == [rows[a] for a in anc] + [-1] * (32 - len(anc))
+                chunk += 1
+    for p in (trees.chain(17), trees.chain(33)):
+        other, _ = L.lumo_tree_plan(np.array([0, len(p)], np.int32), p, np.array([len(p)], np.int32), L.LUMO_POLICY_WY)
+        assert other.n_words == other.o_vis + 2 * other.total_nodes
