@@ -90,7 +90,8 @@ lumo_status check_wy_verify(const lumo_gdn_dims* d, const lumo_tree_desc* desc, 
 }
 
 hipError_t launch_wy_any(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s) {
-    return wy_mfma_shape(d, desc) ? launch_wy(d, desc, a, s) : launch_wyv(d, desc, a, s);
+    if (!wy_mfma_shape(d, desc)) return launch_wyv(d, desc, a, s);
+    return d.op_dtype == LUMO_BF16 ? launch_wy(d, desc, a, s) : launch_wyf(d, desc, a, s);
 }
 
 // Operand preparation: flags, constant and gate parameters; NULL means none.

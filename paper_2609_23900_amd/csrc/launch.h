@@ -74,10 +74,14 @@ constexpr int kWyMaxDepth = kPreStack + 1;  // nodes on a root-to-leaf path (def
 // workspace; operand preparation as in GdnArgs::prep.
 constexpr int kWyvMaxDepth = 32;
 hipError_t launch_wyv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s);
-// Whether the matrix-core WY kernel serves these dimensions and plan: paths of up to
-// kWyMaxDepth nodes, and of up to kDeepStack with a plan that carries the tables for them.
+// The WY form on the fp32 matrix instructions: fp32 operands, d_k = d_v = 128.
+hipError_t launch_wyf(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s);
+
+// Whether a matrix-core WY kernel serves these dimensions and plan (launch_wy for bf16,
+// launch_wyf for fp32 operands): paths of up to kWyMaxDepth nodes, and of up to kDeepStack
+// with a plan that carries the tables for them.
 inline bool wy_mfma_shape(const lumo_gdn_dims& d, const lumo_tree_desc& desc) {
-    return d.op_dtype == LUMO_BF16 && d.d_k == 128 && d.d_v == 128 &&
+    return d.d_k == 128 && d.d_v == 128 &&
            (desc.plan.max_depth <= kWyMaxDepth || deep_section(desc.plan, desc.host_blob) >= 0);
 }
 
