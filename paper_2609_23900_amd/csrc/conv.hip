@@ -18,7 +18,8 @@ namespace {
 
 struct ConvParams {
     const int32_t* blob;
-    int32_t o_req, o_row, o_conv_src, o_node_off, o_dfs;
+    int32_t o_req, o_row, o_conv_src, o_node_off, o_dfs, o_pre_row, o_pre_depth;
+    int32_t n_runs;  // conv_walk_kernel: runs per request
     int32_t n_req, total_nodes, total_rows, n_layers, channels, n_cchunks, act;
     int32_t run;  // nodes per block (1..kNodesPerBlock)
     int32_t pre;  // 1: runs follow each request's preorder; 0: the stored node order
@@ -233,6 +234,160 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvParams p) {
             }
             if (has_c) Vec8<OPT>::st(y + ((long)l * p.total_rows + row) * p.channels + c, acc);
         }
+    }
+}
+
+// Walk of a run (large grids): one wavefront takes one layer, one request's next RUN
+// preorder positions and 64 x 16 bytes of channels, and keeps the x entries of the current
+// root path by depth in LDS (rows 0..2 the history, row 3 + d depth d), so that each x row
+// is loaded once per run: a node at depth d finds its window in rows d, d + 1, d + 2, and its
+// own entry goes into row d + 3. Ancestors before the run are loaded where they are
+// needed: only the first node and every node shallower than all before it in the run have a
+// parent outside, and their three window sources (plan) are copied to LDS up front. The
+// arithmetic is conv_kernel's (the same bits). Bound by HBM: conv_kernel loads every window
+// row from L2 and re-reads x 1.4 to 1.6 times from HBM; this walk reads it once, and a few
+// rows per run again. One-wave blocks, so that a run's serial walk waits for nobody; the
+// grid must hold enough of them (rule and figures in launch_conv). kG: rows loaded ahead.
+template <int OPT, int kG>
+__global__ __launch_bounds__(64) void conv_walk_kernel(ConvParams p) {
+    using T = typename Op<OPT>::T;
+    constexpr int CH = 16 / (int)sizeof(T);  // channels per lane
+    extern __shared__ __attribute__((aligned(16))) uint4 ext[];  // [max_depth + 3][64]
+    const int lane = (int)threadIdx.x;
+    int t = xcd_remap(blockIdx.x, gridDim.x);
+    const int ri = t % p.n_runs;
+    t /= p.n_runs;
+    const int cc = t % p.n_cchunks;
+    t /= p.n_cchunks;
+    const int r = t % p.n_req;
+    const int l = t / p.n_req;
+    const int base = p.blob[p.o_node_off + r];
+    const int N = p.blob[p.o_node_off + r + 1] - base;
+    const int p0 = ri * p.run;
+    const int cnt = min(N - p0, p.run);
+    if (cnt <= 0) return;  // uniform
+    const int c0 = (cc * 64 + lane) * CH;
+    const bool has_c = c0 < p.channels;
+    const int c = has_c ? c0 : p.channels - CH;
+    const T* xl = static_cast<const T*>(p.x) + (long)l * p.total_rows * p.channels;
+    const T* hl = static_cast<const T*>(p.hist) + ((long)r * p.n_layers + l) * 3 * p.channels;
+    T* yl = static_cast<T*>(p.y) + (long)l * p.total_rows * p.channels;
+    // lane i: position p0 + i's row and depth (past the run: the last node's)
+    const int at = base + p0 + min(lane, cnt - 1);
+    const int row_l = p.blob[p.o_pre_row + at];
+    const int dep_l = p.blob[p.o_pre_depth + at];
+    const int node_l = base + p.blob[p.o_dfs + at];
+    int src_l[3];  // the window sources of lane i's node: depths d - 3, d - 2, d - 1
+#pragma unroll
+    for (int e = 0; e < 3; ++e) src_l[e] = p.blob[p.o_conv_src + 4 * node_l + e];
+    auto load = [&](int i) -> uint4 {  // node i's x entry
+        const int row = __builtin_amdgcn_readlane(row_l, min(i, cnt - 1));
+        return *reinterpret_cast<const uint4*>(xl + (long)row * p.channels + c);
+    };
+    uint4 buf[2][kG];
+#pragma unroll
+    for (int i = 0; i < kG; ++i) buf[0][i] = load(i);
+    // depths shallower than every earlier one of the run (lane 0 always)
+    int before = __shfl_up(dep_l, 1);
+    if (lane == 0) before = 0x7fffffff;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(before, off);
+        before = lane >= off ? min(before, o) : before;
+    }
+    uint64_t todo = __ballot(lane < cnt && dep_l < before);
+    int lowest = 0x7fffffff;  // shallowest depth whose entry is on its way
+    while (todo) {            // uniform
+        const int i = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        const int d = __builtin_amdgcn_readlane(dep_l, i);
+#pragma unroll
+        for (int e = 2; e >= 0; --e) {
+            const int depth = d - 3 + e;
+            if (depth >= lowest) continue;
+            const int s = __builtin_amdgcn_readlane(src_l[e], i);
+            const T* from = s >= 0 ? xl + (long)s * p.channels : hl + (long)(-1 - s) * p.channels;
+            __builtin_amdgcn_global_load_lds(reinterpret_cast<const uint4*>(from + c),
+                                             (__attribute__((address_space(3))) void*)&ext[(depth + 3) * 64], 16, 0, 0);
+        }
+        lowest = min(lowest, d - 3);
+    }
+    float wt[4 * CH], b0[CH];
+    const float4* wp = reinterpret_cast<const float4*>(p.w + ((long)l * p.channels + c) * 4);
+#pragma unroll
+    for (int e = 0; e < CH; ++e) {
+        const float4 q = wp[e];
+        wt[4 * e] = q.x; wt[4 * e + 1] = q.y; wt[4 * e + 2] = q.z; wt[4 * e + 3] = q.w;
+        b0[e] = p.bias ? p.bias[(long)l * p.channels + c + e] : 0.f;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the ancestors have landed in LDS
+    struct Win {
+        uint4 e[3];
+    };
+    auto window = [&](int d, Win& w) {
+#pragma unroll
+        for (int e = 0; e < 3; ++e) w.e[e] = ext[(d + e) * 64 + lane];
+    };
+    auto unpack = [](const uint4& w, float (&v)[CH]) {
+        if constexpr (OPT == 1) {
+            Vec8<1>::unpack(w, v);
+        } else {
+            v[0] = __uint_as_float(w.x); v[1] = __uint_as_float(w.y);
+            v[2] = __uint_as_float(w.z); v[3] = __uint_as_float(w.w);
+        }
+    };
+    int d = __builtin_amdgcn_readlane(dep_l, 0);
+    Win cur;
+    window(d, cur);
+    // the group's nodes; each node's entry goes to LDS and the next node's window is read
+    // before the node is computed
+    auto group = [&](int i0, const uint4 (&b)[kG]) {
+#pragma unroll
+        for (int k = 0; k < kG; ++k) {
+            const int i = i0 + k;
+            if (i >= cnt) break;  // uniform
+            ext[(d + 3) * 64 + lane] = b[k];
+            const int dn = __builtin_amdgcn_readlane(dep_l, min(i + 1, cnt - 1));
+            Win nxt;
+            window(dn, nxt);
+            float acc[CH];
+#pragma unroll
+            for (int e = 0; e < CH; ++e) acc[e] = b0[e];
+#pragma unroll
+            for (int tap = 0; tap < 4; ++tap) {
+                float xv[CH];
+                unpack(tap < 3 ? cur.e[tap < 3 ? tap : 0] : b[k], xv);
+#pragma unroll
+                for (int e = 0; e < CH; ++e) acc[e] = __builtin_fmaf(wt[4 * e + tap], xv[e], acc[e]);
+            }
+            if (p.act == 1) {
+#pragma unroll
+                for (int e = 0; e < CH; ++e) acc[e] = acc[e] * __builtin_amdgcn_rcpf(1.f + __expf(-acc[e]));
+            }
+            if (has_c) {
+                T* dst = yl + (long)__builtin_amdgcn_readlane(row_l, i) * p.channels + c;
+                if constexpr (OPT == 1) {
+                    Vec8<1>::st(dst, acc);
+                } else {
+                    *reinterpret_cast<float4*>(dst) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                }
+            }
+            cur = nxt;
+            d = dn;
+        }
+    };
+    for (int i0 = 0; i0 < cnt; i0 += 2 * kG) {
+        if (i0 + kG < cnt) {
+#pragma unroll
+            for (int i = 0; i < kG; ++i) buf[1][i] = load(i0 + kG + i);
+        }
+        group(i0, buf[0]);
+        if (i0 + kG >= cnt) break;
+        if (i0 + 2 * kG < cnt) {
+#pragma unroll
+            for (int i = 0; i < kG; ++i) buf[0][i] = load(i0 + 2 * kG + i);
+        }
+        group(i0 + kG, buf[1]);
     }
 }
 
@@ -475,6 +630,30 @@ hipError_t launch_conv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const
     p.w = a.w;
     p.bias = a.bias;
     p.y = a.y;
+    p.o_pre_row = pl.o_pre_row;
+    p.o_pre_depth = pl.o_pre_depth;
+    // The walk over runs, where the grid holds at least 2,048 of its one-wave blocks (eight per
+    // CU) and a root path fits in 20 KB of LDS (eight blocks per CU). fp32 operands take runs
+    // of 16 nodes: 8 requests x 12 layers x 64 nodes x 8,192 channels 125 -> 82 us, 3 layers
+    // 22.9 -> 18.2 us; below the line 11.8 against 11.3 us, paths of 32 nodes 22.9 against 26.9.
+    // bf16 rows are half as long, so a run has to be longer to pay for its start: 64
+    // nodes, with rows loaded eight ahead (32 requests x 256 nodes 69 -> 57 us; 64 requests
+    // of 16 and 128 nodes, below the line, 36 against 49 us).
+    const bool bf = d.op_dtype == LUMO_BF16;
+    const int run_nodes = bf ? 64 : 16, lane_channels = bf ? 8 : 4;
+    const int walk_chunks = (a.channels + 64 * lane_channels - 1) / (64 * lane_channels);
+    if (pl.max_depth + 3 <= 20 && (long)pl.total_nodes / run_nodes * d.n_layers * walk_chunks >= 2048) {
+        p.run = run_nodes;
+        p.n_runs = (pl.max_nodes + p.run - 1) / p.run;
+        p.n_cchunks = walk_chunks;
+        const long nb = (long)p.n_runs * p.n_cchunks * d.n_req * d.n_layers;
+        const size_t lds = (size_t)(pl.max_depth + 3) * 64 * sizeof(uint4);
+        if (bf)
+            hipLaunchKernelGGL((conv_walk_kernel<1, 8>), dim3((unsigned)nb), dim3(64), lds, s, p);
+        else
+            hipLaunchKernelGGL((conv_walk_kernel<0, 4>), dim3((unsigned)nb), dim3(64), lds, s, p);
+        return hipGetLastError();
+    }
     // runs of 32 nodes, halved (down to 4) while the grid has fewer than four blocks per
     // CU: a block's node batches are loaded one after the other, so small grids (one
     // layer of a batch) finish sooner with more, shorter runs
