@@ -7,10 +7,10 @@
 //   2. replay kernel  one wavefront per (request, layer, value head, value tile):
 //                     load the pre-tree state tile, apply the recorded updates of the
 //                     path with the same row update the verifier uses, store in place;
-//                     before the loop the path's first key rows are copied to LDS
-//                     (direct global-to-LDS loads, in flight with the state load) and
-//                     its rows, decays, betas and value entries are fetched into lanes.
-//                     Skipped when the state is NULL (publication deferred).
+//                     the path's key rows, gates and value entries are staged in LDS
+//                     while the state loads are in flight. Two forms with the same bits
+//                     (tiles of 16 columns, and of 64 for large state banks). Skipped
+//                     when the state is NULL (publication deferred).
 // Empty or invalid paths leave the state and the history untouched.
 #include "device_common.h"
 #include "internal.h"
@@ -56,10 +56,143 @@ __global__ __launch_bounds__(256) void path_kernel(PathParams p) {
 struct ReplayParams {
     const int32_t* blob;
     int32_t o_node_off, o_row;
-    int32_t max_path, n_layers, total_rows, h_k, h_v, d_v, group, n_vtiles;
+    int32_t max_path, n_layers, total_rows, h_k, h_v, d_v, group, n_ct, nwk, n_wb, n_vtiles;
     PrepArgs prep;  // operand preparation of the path's k, g, beta
 };
 
+// Replay of the path into the state, in the layout of the single-launch scan
+// (verify_scan.hip): a wavefront takes 16 value columns, lane 4 c + r the keys i = r (mod 4)
+// of column c, so that each lane owns one of Dot4's four chains of its column and two quad
+// exchanges add them in Dot4's order: every value is computed with the operations, and in the
+// order, of the verifier's row update (bitwise the same state). A block is four such
+// wavefronts of one key head, which share the path's key rows: kReplayChunk entries at a
+// time, converted to fp32 and split by i % 4 on the way into LDS, while the state loads are
+// in flight. With query/key normalisation each key's factor is one fma chain over the
+// elements in index order, as in the scan. Bound by HBM (the state is read and written
+// once).
+constexpr int kReplayChunk = 16;
+
+template <int DK, int OPT>
+__global__ __launch_bounds__(256, 4) void replay_kernel(ReplayParams p, const typename Op<OPT>::T* __restrict__ k,
+                                                   const typename Op<OPT>::T* __restrict__ v,
+                                                   const float* __restrict__ g, const float* __restrict__ beta,
+                                                   float* __restrict__ state, const int32_t* __restrict__ path_out,
+                                                   const int32_t* __restrict__ path_len) {
+    using T = typename Op<OPT>::T;
+    constexpr int KC = kReplayChunk;
+    constexpr int E = DK / 4;     // keys per lane
+    constexpr int RS = E + 4;     // floats per residue row (padded: the four rows on different banks)
+    constexpr int EPT = DK / 16;  // row elements a thread stages (16 threads per entry)
+    struct __attribute__((aligned(EPT * sizeof(T)))) Piece {
+        T e[EPT];
+    };
+    __shared__ __attribute__((aligned(16))) float rows[KC][4 * RS];
+    __shared__ __attribute__((aligned(16))) float vals[4][KC][16];  // per wave
+    __shared__ float2 gates[4][KC];                                // per wave: decay, beta
+    __shared__ float norm[KC];                                     // key factors (1 without normalisation)
+    int t = (int)blockIdx.x;  // (dealing whole requests to an XCD leaves some XCDs the long paths: 68 against 62 us)
+    const int wb = t % p.n_wb;
+    t /= p.n_wb;
+    const int hk = t % p.h_k;
+    t /= p.h_k;
+    const int l = t % p.n_layers;
+    const int r = t / p.n_layers;
+    const int len = path_len[r];
+    if (len <= 0) return;  // uniform over the block
+    const int tid = (int)threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63;
+    const int gw = wb * 4 + wave;
+    const bool wact = gw < p.nwk;  // uniform: idle waves stage rows only
+    const int h = hk * p.group + (wact ? gw / p.n_ct : 0);
+    const int j0 = (wact ? gw % p.n_ct : 0) * 16;
+    const int c = lane >> 2, res = lane & 3;
+    const int base = p.blob[p.o_node_off + r];
+    const int32_t* path = path_out + (long)r * p.max_path;
+    const int sn = tid >> 4, sp = tid & 15;
+    // entries past the path repeat its last one (staged, never applied)
+    int prow = p.blob[p.o_row + base + path[min(sn, len - 1)]];  // row of the entry whose key this thread stages
+    int wrow = p.blob[p.o_row + base + path[min(c, len - 1)]];   // row of the entry whose values this lane stages
+    float* st = state + (((long)r * p.n_layers + l) * p.h_v + h) * (long)DK * p.d_v + (long)res * p.d_v + j0 + c;
+    float S[E];
+    if (wact) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) S[i] = st[(long)(4 * i) * p.d_v];
+    }
+    const bool qkn = (p.prep.flags & LUMO_PREP_QK_NORM) != 0;  // uniform
+    for (int e0 = 0; e0 < len; e0 += KC) {
+        if (e0 > 0) {
+            prow = p.blob[p.o_row + base + path[min(e0 + sn, len - 1)]];
+            wrow = p.blob[p.o_row + base + path[min(e0 + c, len - 1)]];
+            __syncthreads();  // the previous entries have been applied by every wave
+        }
+        const Piece kp = *reinterpret_cast<const Piece*>(k + (((long)l * p.total_rows + prow) * p.h_k + hk) * DK + EPT * sp);
+        const long gi = ((long)l * p.total_rows + wrow) * p.h_v + h;
+        struct __attribute__((aligned(4 * sizeof(T)))) V4 {
+            T e[4];
+        };
+        const V4 vp = *reinterpret_cast<const V4*>(v + gi * p.d_v + j0 + 4 * res);
+        float gv = g[gi], bv = beta[gi];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int i = EPT * sp + e;
+            rows[sn][(i & 3) * RS + (i >> 2)] = Op<OPT>::ld(kp.e, e);
+        }
+        *reinterpret_cast<float4*>(&vals[wave][c][4 * res]) =
+            make_float4(Op<OPT>::ld(vp.e, 0), Op<OPT>::ld(vp.e, 1), Op<OPT>::ld(vp.e, 2), Op<OPT>::ld(vp.e, 3));
+        if (res == 0) {
+            if (p.prep.flags & LUMO_PREP_RAW_GATES) {
+                const int lh = l * p.h_v + h;
+                gv = raw_log_alpha(gv, p.prep.a_log[lh], p.prep.dt_bias[lh]);
+                bv = raw_beta(bv);
+            }
+            gates[wave][c] = make_float2(__expf(gv), bv);
+        }
+        __syncthreads();
+        if (qkn) {
+            if (tid < KC) {
+                float ss = 0.f;
+                for (int i = 0; i < DK; ++i) {
+                    const float x = rows[tid][(i & 3) * RS + (i >> 2)];
+                    ss = __builtin_fmaf(x, x, ss);
+                }
+                norm[tid] = __builtin_amdgcn_rsqf(ss + p.prep.qk_eps);
+            }
+            __syncthreads();
+        }
+        if (!wact) continue;
+        const int ne = min(len - e0, KC);
+        for (int n = 0; n < ne; ++n) {
+            const float2 ab = gates[wave][n];
+            const float ks = qkn ? norm[n] : 1.f;
+            const float vj = vals[wave][n][c];
+            const float* kr = &rows[n][res * RS];
+            float kf[E];
+#pragma unroll
+            for (int i = 0; i < E; i += 4) {
+                const float4 w = *reinterpret_cast<const float4*>(kr + i);
+                kf[i] = w.x;
+                kf[i + 1] = w.y;
+                kf[i + 2] = w.z;
+                kf[i + 3] = w.w;
+            }
+            float u = 0.f;
+#pragma unroll
+            for (int i = 0; i < E; ++i) u = __builtin_fmaf(S[i], kf[i], u);
+            u = quad_sum(u);
+            const float delta = ab.y * __builtin_fmaf(-ab.x, u * ks, vj) * ks;
+#pragma unroll
+            for (int i = 0; i < E; ++i) S[i] = __builtin_fmaf(delta, kf[i], ab.x * S[i]);
+        }
+    }
+    if (wact) {
+#pragma unroll
+        for (int i = 0; i < E; ++i) st[(long)(4 * i) * p.d_v] = S[i];
+    }
+}
+
+// The same replay with 64 value columns per wavefront, one per lane, for state banks beyond
+// the Infinity Cache (launch_replay_dk). The same bits: gdn_row_update's order.
 // Path entries whose key row, row, decay, beta and value are fetched before the loop.
 constexpr int kPrefetch = 16;
 
@@ -158,7 +291,7 @@ __device__ __forceinline__ void replay_stage(const ReplayParams& p, const typena
 }
 
 template <int DK, int OPT>
-__global__ __launch_bounds__(64, 2) void replay_kernel(ReplayParams p, const typename Op<OPT>::T* __restrict__ k,
+__global__ __launch_bounds__(64, 2) void replay_tile_kernel(ReplayParams p, const typename Op<OPT>::T* __restrict__ k,
                                                    const typename Op<OPT>::T* __restrict__ v,
                                                    const float* __restrict__ g, const float* __restrict__ beta,
                                                    float* __restrict__ state, const int32_t* __restrict__ path_out,
@@ -325,19 +458,36 @@ __global__ __launch_bounds__(256) void path_hist_layers_kernel(PathParams pp, Hi
 }
 
 template <int DK, int OPT>
-void launch_replay_dk(dim3 grid, hipStream_t s, const ReplayParams& p, const CommitArgs& a) {
+void launch_replay_dk(const lumo_gdn_dims& d, hipStream_t s, ReplayParams& p, const CommitArgs& a) {
     using T = typename Op<OPT>::T;
-    hipLaunchKernelGGL((replay_kernel<DK, OPT>), grid, dim3(64), 0, s, p, static_cast<const T*>(a.k),
-                       static_cast<const T*>(a.v), a.g, a.beta, a.state, a.path_out, a.path_len);
+    const long heads = (long)d.n_req * d.n_layers * d.h_v;
+    // 16-column wavefronts keep twice as much of the state in flight, and win while the state
+    // bank stays in the 256 MB Infinity Cache between calls (8 requests x 32 heads, d =
+    // 128, bf16: 6 layers 53.8 -> 41.7 us, 12 layers 85.6 -> 72.8 us; fp32 12 layers 103 -> 75
+    // us). Beyond it the 64-column form, which reads whole 256-byte rows, is as fast or
+    // faster (18 layers 122 against 136 us, 48 layers 334 against 339 us).
+    if (heads * DK * d.d_v * (long)sizeof(float) <= (256l << 20)) {
+        p.n_ct = d.d_v / 16;
+        p.nwk = p.group * p.n_ct;
+        p.n_wb = (p.nwk + 3) / 4;
+        const long blocks = (long)d.n_req * d.n_layers * d.h_k * p.n_wb;
+        hipLaunchKernelGGL((replay_kernel<DK, OPT>), dim3((unsigned)blocks), dim3(256), 0, s, p, static_cast<const T*>(a.k),
+                           static_cast<const T*>(a.v), a.g, a.beta, a.state, a.path_out, a.path_len);
+    } else {
+        p.n_vtiles = (d.d_v + 63) / 64;
+        hipLaunchKernelGGL((replay_tile_kernel<DK, OPT>), dim3((unsigned)(heads * p.n_vtiles)), dim3(64), 0, s, p,
+                           static_cast<const T*>(a.k), static_cast<const T*>(a.v), a.g, a.beta, a.state, a.path_out,
+                           a.path_len);
+    }
 }
 
 template <int OPT>
-hipError_t launch_replay(int dk, dim3 grid, hipStream_t s, const ReplayParams& p, const CommitArgs& a) {
-    switch (dk) {
-        case 16: launch_replay_dk<16, OPT>(grid, s, p, a); break;
-        case 32: launch_replay_dk<32, OPT>(grid, s, p, a); break;
-        case 64: launch_replay_dk<64, OPT>(grid, s, p, a); break;
-        default: launch_replay_dk<128, OPT>(grid, s, p, a); break;
+hipError_t launch_replay(const lumo_gdn_dims& d, hipStream_t s, ReplayParams& p, const CommitArgs& a) {
+    switch (d.d_k) {
+        case 16: launch_replay_dk<16, OPT>(d, s, p, a); break;
+        case 32: launch_replay_dk<32, OPT>(d, s, p, a); break;
+        case 64: launch_replay_dk<64, OPT>(d, s, p, a); break;
+        default: launch_replay_dk<128, OPT>(d, s, p, a); break;
     }
     return hipGetLastError();
 }
@@ -384,11 +534,8 @@ hipError_t launch_commit(const lumo_gdn_dims& d, const lumo_tree_desc& desc, con
     rp.h_v = d.h_v;
     rp.d_v = d.d_v;
     rp.group = d.h_v / d.h_k;
-    rp.n_vtiles = (d.d_v + 63) / 64;
     rp.prep = a.prep;
-    const long blocks = (long)d.n_req * d.n_layers * d.h_v * rp.n_vtiles;
-    e = d.op_dtype == LUMO_BF16 ? launch_replay<1>(d.d_k, dim3((unsigned)blocks), s, rp, a)
-                                : launch_replay<0>(d.d_k, dim3((unsigned)blocks), s, rp, a);
+    e = d.op_dtype == LUMO_BF16 ? launch_replay<1>(d, s, rp, a) : launch_replay<0>(d, s, rp, a);
     if (e != hipSuccess) return e;
     }
 

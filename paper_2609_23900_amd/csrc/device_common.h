@@ -168,6 +168,16 @@ __device__ __forceinline__ float row_group_sum(float x) {
     return __uint_as_float(b[0]) + __uint_as_float(b[1]);
 }
 
+// x of the lane whose index differs in bit 0 (quad_perm 1,0,3,2) or 1 (2,3,0,1)
+template <int CTRL> __device__ __forceinline__ float quad_swap(float x) {
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+// (s0 + s1) + (s2 + s3) of a quad's four partial sums, in all four lanes
+__device__ __forceinline__ float quad_sum(float s) {
+    s = s + quad_swap<0xB1>(s);
+    return s + quad_swap<0x4E>(s);
+}
+
 // ---------------------------------------------------------------- launch geometry
 // Workgroups are dispatched round-robin over the 8 XCDs (each with its own L2).
 // Remap so that consecutive logical block ids run on the same XCD: blocks that

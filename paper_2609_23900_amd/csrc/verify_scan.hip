@@ -122,16 +122,6 @@ struct ScanTreeParams {
     int32_t n_layers, total_rows, h_k, h_v, d_v, group, n_ct, nwk, n_wb;
 };
 
-// x of the lane whose index differs in bit 0 (quad_perm 1,0,3,2) or 1 (2,3,0,1)
-template <int CTRL> __device__ __forceinline__ float quad_swap(float x) {
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xf, 0xf, true));
-}
-// (s0 + s1) + (s2 + s3) of a quad's four partial sums, in all four lanes
-__device__ __forceinline__ float quad_sum(float s) {
-    s = s + quad_swap<0xB1>(s);
-    return s + quad_swap<0x4E>(s);
-}
-
 template <int DK, int OPT, int NS>
 __global__ __launch_bounds__(256, 2) void scan_tree_kernel(ScanTreeParams p,
                                                            const typename Op<OPT>::T* __restrict__ q,
