@@ -14,7 +14,7 @@
 // the time of the fp32 ones, whose chains also round more often. Error of the
 // outputs against 64-bit arithmetic: 8.9e-8 (one fp32-MFMA chain of 128 terms 1.6e-7; the
 // vector-ALU kernel that served these shapes before 9.3e-8). 8 requests x 12 layers x 64 nodes x 32
-// heads: 221 us (that kernel 516 us), 1 layer 29 us (148 us).
+// heads: 211 us (that kernel 516 us), 1 layer 28 us (148 us).
 //
 // A block serves (request, layer, value head) with four wavefronts of 32 state columns and
 // walks the request's nodes in depth-first preorder, 32 (a chunk) at a time. The threads load
@@ -89,9 +89,9 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
     __shared__ float nrm[kTileRows];  // QKN: 1/|row| of [stack keys | chunk keys | chunk queries]
     const int tid = (int)threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63;
-    // taken anew at every chunk (opaque), so that LDS addresses derived from them are recomputed
-    // rather than kept live across the loop
+    // the lane index is made opaque at every chunk, so that what derives from it (LDS
+    // addresses) is recomputed rather than kept live across the loop
+    int lane = tid & 63;
     int lq = lane & 15, lg = lane >> 4;
 
     // the blocks of a (request, layer) on one XCD (shared rows), the units over all of them
@@ -115,7 +115,7 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
     int t = lane % kTile;  // node of this lane in the chunk views
     const int j0 = kCW * wave;
     unsigned pc = 2 * lq + (lg & 1);  // this lane's column after the exchange of the products
-    const bool hiB = lane >= kTile;
+    bool hiB = lane >= kTile;
 
     // Chunk views of a lane: node t's row (positions past the end repeat the last node, so
     // that padding slots are exact copies of it), and the rows whose pieces the thread
@@ -339,7 +339,14 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
         const bool more = c0 + kTile < N;
         const bool two = c0 + kTile / 2 < N;  // the second half holds real nodes
         const int rowN = rowC.n;  // this chunk's row of node t
-        asm volatile("" : "+v"(lq), "+v"(lg), "+v"(t), "+v"(pc), "+v"(sr), "+v"(sp));
+        asm volatile("" : "+v"(lane));
+        lq = lane & 15;
+        lg = lane >> 4;
+        t = lane % kTile;
+        hiB = lane >= kTile;
+        pc = 2 * lq + (lg & 1);
+        sr = 4 * wave + lg;
+        sp = lq;
         stage_store(stg);  // (every wave has read the previous chunk's rows: barrier below)
         if (wave == 0) {  // decays of the candidates
             const float an = __expf(rawg ? raw_log_alpha(info.gn, alog, dtb) : info.gn);
