@@ -48,6 +48,7 @@ TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "traffic.json")
 VERIFY_SOURCES = {
     "wy": ["verify_wy.hip", "verify_wy_body.inc", "verify_wy.h", "device_common.h", "internal.h", "launch.h"],
     "paths": ["verify_scan.hip", "device_common.h", "internal.h", "launch.h"],
+    "wyf": ["verify_wyf.hip", "device_common.h", "internal.h", "launch.h"],
     "wyv": ["verify_wyv.hip", "device_common.h", "internal.h", "launch.h"],
     "attention": ["attention.hip", "device_common.h", "internal.h", "launch.h"],
     "select": ["select.hip", "select.h", "device_common.h"],
@@ -503,6 +504,9 @@ def arithmetic_label(wl, policy, args):
     import paper_2609_23900_amd as L
     ops_t = "bf16" if wl.op_dtype == 1 else "f32"
     if policy == L.LUMO_POLICY_WY and wl.op_dtype == 0:
+        if wl.d_k == 128 and wl.d_v == 128:
+            return (f"{ops_t} operands/outputs, f32 state; WY form, every factor of a dot product over the keys as "
+                    "three bf16 parts (24 bits) on MFMA, f32 accumulate")
         return f"{ops_t} operands/outputs, f32 state; WY form on the vector ALUs in f32"
     if policy == L.LUMO_POLICY_WY:
         core = "R0.[K|Q] on bf16 MFMA with R0 split into bf16 hi+lo (16 significant bits), f32 accumulate"
@@ -525,8 +529,8 @@ def main():
                     help="prepare operands in the kernels (query/key normalisation, gates from raw "
                          "inputs; wy policy): g and beta are then read as raw inputs")
     ap.add_argument("--f32", action="store_true",
-                    help="fp32 operands and outputs (the wy policy then runs its vector-ALU kernel, and the "
-                         "commit replays eagerly: the deferred publication lives in the matrix-core kernel)")
+                    help="fp32 operands and outputs (the wy policy then runs its fp32 kernels, and the "
+                         "commit replays eagerly: the deferred publication lives in the bf16 kernel)")
     ap.add_argument("--copy-probe", action="store_true", help="only run the counter-calibration copy")
     ap.add_argument("--attention", action="store_true", help="only run the tree-attention benchmark")
     ap.add_argument("--select", action="store_true", help="only run the draft-selection benchmark")
@@ -691,8 +695,10 @@ def main():
         roof = {"bound": "alu", "achieved": round(ach, 2), "peak": PEAK_VALU_F32_TFS,
                 "unit": "TFLOP/s", "frac": round(ach / PEAK_VALU_F32_TFS, 4), "traffic": None}
     mode = "deferred" if deferred else "eager"
-    if policy == L.LUMO_POLICY_WY and wl.op_dtype == 0:  # the vector-ALU WY kernel
-        tr = recorded_traffic("wyv", args.config + "_f32", mode)
+    f32_wy = policy == L.LUMO_POLICY_WY and wl.op_dtype == 0
+    f32_mfma = f32_wy and wl.d_k == 128 and wl.d_v == 128  # otherwise the vector-ALU WY kernel
+    if f32_wy:
+        tr = recorded_traffic("wyf" if f32_mfma else "wyv", args.config + "_f32", mode)
     else:
         tr = recorded_traffic(args.policy, args.config + ("_f32" if wl.op_dtype == 0 else ""),
                               "fused" if args.fused else mode)
@@ -702,7 +708,8 @@ def main():
                            "source": "profiles/traffic.json"}
     roof["kernel"] = ("tree conv + verify + publication of the previous path (one kernel)" if args.fused
                       else "verify + publication of the previous path" if deferred
-                      else "verify (WY form on the vector ALUs)" if policy == L.LUMO_POLICY_WY and wl.op_dtype == 0
+                      else "verify (WY form, fp32 factors as three bf16 parts on MFMA)" if f32_mfma
+                      else "verify (WY form on the vector ALUs)" if f32_wy
                       else "verify")
     roof["per_launch"] = (f"{ab['verify_flops'] / 1e9:.2f} GFLOP, {vb / 1e6:.1f} MB algorithmic per verify call")
     kernels = {
