@@ -24,6 +24,12 @@
 // swz a rotation of t's low four bits: the 16 keys of a K fragment read take 16 different
 // slots, and the four keys of a transposing V read (ds_read_b64_tr_b16: within 16 lanes,
 // lane i receives element i % 4 of lanes 4 e + i / 4, e = 0..3) four different slot pairs.
+// The probabilities of a tile are taken relative to the row's largest score in that tile, so
+// that its largest is exactly 1 when they are rounded to bf16, and the tile's product is added
+// to the output with its weight relative to the running maximum: the rounding is that of
+// one range per tile, however long the ranges are. Relative to the running maximum
+// itself, 8 requests of 64 nodes x 32 heads over 16,384 tokens had an error of 2.26e-3 against
+// 64 bits instead of 2.09e-3 (bf16 outputs alone 1.7e-3), in 147 us instead of 156 us.
 // Tiles of 64 keys, double-buffered. Visibility inside the tree comes from the plan's
 // preorder intervals; only ragged context tiles and tree tiles are masked.
 #include <mutex>
@@ -222,13 +228,17 @@ __global__ __launch_bounds__(64 * kAW, 2) void attn_kernel(AttnParams p) {
                         if (sl >= N || pos[t] < iv.x || pos[t] >= iv.y) s[t][tt][x] = -INFINITY;
                 }
         }
+        // the tile's probabilities relative to the row's largest score in the tile (never above
+        // 1), and the weight w of the tile relative to the running maximum
+        float w[R];
 #pragma unroll
         for (int t = 0; t < R; ++t) {
             float mt = fmaxf(fmaxf(s[t][0][0], s[t][0][1]), fmaxf(s[t][0][2], s[t][0][3]));
 #pragma unroll
             for (int tt = 1; tt < kAT / 16; ++tt)
                 mt = fmaxf(mt, fmaxf(fmaxf(s[t][tt][0], s[t][tt][1]), fmaxf(s[t][tt][2], s[t][tt][3])));
-            const float mn = fmaxf(mx[t], rows_max(mt) * p.scale_log2);
+            mt = fmaxf(rows_max(mt) * p.scale_log2, -1e30f);  // finite also where no key is visible
+            const float mn = fmaxf(mx[t], mt);
             if (__any(mn > mx[t])) {  // uniform; otherwise the factor is exactly 1
                 const float corr = __builtin_amdgcn_exp2f(mx[t] - mn);
                 mx[t] = mn;
@@ -238,35 +248,40 @@ __global__ __launch_bounds__(64 * kAW, 2) void attn_kernel(AttnParams p) {
 #pragma unroll
                     for (int x = 0; x < 4; ++x) o[t][dt][x] *= corr;
             }
+            w[t] = __builtin_amdgcn_exp2f(mt - mn);
             float ls = 0.f;
 #pragma unroll
             for (int tt = 0; tt < kAT / 16; ++tt)
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
-                    s[t][tt][x] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][tt][x], p.scale_log2, -mn));
+                    s[t][tt][x] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[t][tt][x], p.scale_log2, -mt));
                     ls += s[t][tt][x];
                 }
-            lsum[t] += ls;
+            lsum[t] = __builtin_fmaf(w[t], ls, lsum[t]);
         }
-        // O^T += V^T P^T over the two 32-key halves
+        bf16x8 pw[2][R];  // the two 32-key halves
 #pragma unroll
-        for (int kh = 0; kh < 2; ++kh) {
-            bf16x8 pw[R];
+        for (int kh = 0; kh < 2; ++kh)
 #pragma unroll
             for (int t = 0; t < R; ++t)
-                pw[t] = as_bf16x8(make_uint4(f32x2_to_bf16x2(s[t][2 * kh][0], s[t][2 * kh][1]),
-                                             f32x2_to_bf16x2(s[t][2 * kh][2], s[t][2 * kh][3]),
-                                             f32x2_to_bf16x2(s[t][2 * kh + 1][0], s[t][2 * kh + 1][1]),
-                                             f32x2_to_bf16x2(s[t][2 * kh + 1][2], s[t][2 * kh + 1][3])));
-            // transposing reads: lane j of a 16-lane group reads dims 16 dt + 4 (j % 4) .. + 3
-            // of key 32 kh + 4 (lane / 16) + j / 4 (and of that key + 16), and receives dim
-            // 16 dt + j of keys 32 kh + 4 (lane / 16) + e (and + 16 + e), e = 0..3
-            const int t1 = 32 * kh + 4 * lg + (lq >> 2), t2 = t1 + 16;
-            const char* vb = reinterpret_cast<const char*>(vt);
+                pw[kh][t] = as_bf16x8(make_uint4(f32x2_to_bf16x2(s[t][2 * kh][0], s[t][2 * kh][1]),
+                                                 f32x2_to_bf16x2(s[t][2 * kh][2], s[t][2 * kh][3]),
+                                                 f32x2_to_bf16x2(s[t][2 * kh + 1][0], s[t][2 * kh + 1][1]),
+                                                 f32x2_to_bf16x2(s[t][2 * kh + 1][2], s[t][2 * kh + 1][3])));
+        // O^T += w V^T P^T. Transposing reads: lane j of a 16-lane group reads dims 16 dt + 4 (j
+        // % 4) .. + 3 of key 32 kh + 4 (lane / 16) + j / 4 (and of that key + 16), and receives
+        // dim 16 dt + j of keys 32 kh + 4 (lane / 16) + e (and + 16 + e), e = 0..3
+        const char* vb = reinterpret_cast<const char*>(vt);
 #pragma unroll
-            for (int dt = 0; dt < kAD / 16; ++dt) {
-                const int sg = 2 * dt + ((lq & 3) >> 1);  // 16-byte dim segment, then its half
-                const int hb = 8 * (lq & 1);
+        for (int dt = 0; dt < kAD / 16; ++dt) {
+            const int sg = 2 * dt + ((lq & 3) >> 1);  // 16-byte dim segment, then its half
+            const int hb = 8 * (lq & 1);
+            f32x4 acc[R];
+#pragma unroll
+            for (int t = 0; t < R; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kh = 0; kh < 2; ++kh) {
+                const int t1 = 32 * kh + 4 * lg + (lq >> 2), t2 = t1 + 16;
                 const v4i16 r1 =
                     __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16*)(vb + (t1 * 16 + (sg ^ swz(t1))) * 16 + hb));
                 const v4i16 r2 =
@@ -275,8 +290,12 @@ __global__ __launch_bounds__(64 * kAW, 2) void attn_kernel(AttnParams p) {
                 const bf16x8 va = as_bf16x8(make_uint4(a1.x, a1.y, a2.x, a2.y));
 #pragma unroll
                 for (int t = 0; t < R; ++t)
-                    o[t][dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pw[t], o[t][dt], 0, 0, 0);
+                    acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va, pw[kh][t], acc[t], 0, 0, 0);
             }
+#pragma unroll
+            for (int t = 0; t < R; ++t)
+#pragma unroll
+                for (int x = 0; x < 4; ++x) o[t][dt][x] = __builtin_fmaf(w[t], acc[t][x], o[t][dt][x]);
         }
     };
 

@@ -172,3 +172,42 @@ def test_tree_attention_row_and_range_edges(h_q, h_kv, nodes, n_ctx, n_split):
     say(f"[gpu] tree attention edges h_q={h_q} h_kv={h_kv} nodes={nodes} ctx={n_ctx} n_split={n_split}")
     o, lse = run_gpu(parents, n_rows, node_off, ctx_off, a, h_q, h_kv, n_split, scale)
     check(parents, row_off, total, ctx_off, a, o, lse, h_q, h_kv, scale)
+
+
+@pytest.mark.parametrize("nodes,tiles", [(1, 5), (17, 18)])  # one and two row tiles per wave
+def test_tree_attention_probabilities_relative_to_each_tile(nodes, tiles):
+    """Each 64-key tile holds one key that matters, with scores that rise and fall from tile to
+    tile, and the root's value cancels the sum. Probabilities are rounded to bf16 relative to
+    their tile's largest, so the keys that matter have probability 1 in their tile, exactly,
+    and what remains is fp32 arithmetic (scores, exponentials and weights to a few units of
+    2^-23 each, so 2^-18 of the sum of magnitudes) and the bf16 rounding of the result
+    (2^-8 of it). Relative to a running maximum across tiles the rounding alone is 2^-9 of the
+    terms."""
+    rng = np.random.default_rng(31)
+    n_ctx, h_q = 64 * tiles, 8
+    k = np.zeros((n_ctx, 1, D), np.float32)
+    k[:, 0, 0] = -128.0  # e^-128 of the others
+    peak = 64 * np.arange(tiles) + rng.integers(0, 64, tiles)
+    k[peak, 0, 0] = ops.bf16_bits_to_f32(ops.to_bf16_bits(rng.uniform(0, 2, tiles).astype(np.float32)))
+    root_key = 1.3125
+    kt = np.zeros((nodes, 1, D), np.float32)
+    kt[:, 0, 0] = -128.0
+    kt[0, 0, 0] = root_key
+    q = np.zeros((nodes, h_q, D), np.float32)
+    q[:, :, 0] = 8.0
+    scale = 0.125  # score = key entry 0, exactly
+    v = ops.bf16_bits_to_f32(bf16(rng, (n_ctx, 1, D))).astype(np.float64)
+    p = np.exp(k[peak, 0, 0].astype(np.float64))
+    vt = np.zeros((nodes, 1, D), np.float32)
+    vt[0, 0] = -(p @ v[peak, 0]) / np.exp(root_key)
+    a = {n: ops.to_bf16_bits(np.asarray(x, np.float32)) for n, x in dict(q=q, k_tree=kt, v_tree=vt, k_ctx=k, v_ctx=v).items()}
+    vt = ops.bf16_bits_to_f32(a["v_tree"]).astype(np.float64)
+    mass = p.sum() + np.exp(root_key)
+    ref = (p @ v[peak, 0] + np.exp(root_key) * vt[0, 0]) / mass
+    size = (p @ np.abs(v[peak, 0]) + np.exp(root_key) * np.abs(vt[0, 0])) / mass
+    say(f"[gpu] tree attention, one key per tile: nodes={nodes} tiles={tiles}")
+    o, lse = run_gpu([trees.chain(nodes)], [nodes], np.array([0, nodes], np.int32), np.array([0, n_ctx], np.int32), a, h_q,
+                     1, 1, scale)
+    err = np.abs(o - ref) - np.abs(ref) * 2.0 ** -8
+    assert err.max() <= 2.0 ** -18 * size.max(), float((err / size).max())
+    assert np.all(np.abs(lse - np.log(mass)) <= 2e-6)
