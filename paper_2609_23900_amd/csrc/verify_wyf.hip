@@ -6,10 +6,12 @@
 // ancestors a_m of node t.
 //
 // Every factor of a dot product over the keys keeps its 24 bits: x = hi + mid + lo, three
-// bf16 values (hi the upper half of x, mid the remainder rounded to bf16, lo what is left,
-// exactly), and a product is the six partial products of at least 2^-16 of its size
-// (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid), exact in fp32; what is dropped is below
-// 2^-23 of it. The five small ones are summed first and the four steps of hi hi last, so
+// bf16 values (hi is x rounded to bf16, mid the remainder rounded to bf16, lo what is left,
+// exactly, where it is a normal number, |x| > 2^-102), and a product is the six partial products
+// (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid), exact in fp32. With |mid| <= 2^-8 and |lo|
+// <= 2^-17 of x's power of two, what is dropped (mid lo, lo mid, lo lo) is at most 2^-24 of
+// the product; with hi cut off instead of rounded it was up to 2^-22. The five small
+// ones are summed first and the four steps of hi hi last, so
 // that only those round at the size of the result. Six bf16 matrix instructions take 6/16 of
 // the time of the fp32 ones, whose chains also round more often. Error of the
 // outputs against 64-bit arithmetic: 8.9e-8 (one fp32-MFMA chain of 128 terms 1.6e-7; the
@@ -66,9 +68,8 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 w) { return __builtin_bit_cast
 
 // Two fp32 values as packed bf16 parts.
 __device__ __forceinline__ void split3(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-    const uint32_t b0 = __float_as_uint(x0), b1 = __float_as_uint(x1);
-    hi = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
-    const float r0 = x0 - __uint_as_float(b0 & 0xffff0000u), r1 = x1 - __uint_as_float(b1 & 0xffff0000u);
+    hi = f32x2_to_bf16x2(x0, x1);
+    const float r0 = x0 - bf16_lo(hi), r1 = x1 - bf16_hi(hi);
     mid = f32x2_to_bf16x2(r0, r1);
     lo = f32x2_to_bf16x2(r0 - bf16_lo(mid), r1 - bf16_hi(mid));
 }
@@ -296,9 +297,7 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
 #pragma unroll
                 for (int e = 0; e < 8; ++e) asm volatile("" : "+v"(R0[ct][kb][e]));
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    hi[e] = __builtin_amdgcn_perm(__float_as_uint(R0[ct][kb][2 * e + 1]), __float_as_uint(R0[ct][kb][2 * e]),
-                                                  0x07060302u);
+                for (int e = 0; e < 4; ++e) hi[e] = f32x2_to_bf16x2(R0[ct][kb][2 * e], R0[ct][kb][2 * e + 1]);
                 rh[ct] = as_bf16x8(make_uint4(hi[0], hi[1], hi[2], hi[3]));
             }
 #pragma unroll

@@ -116,3 +116,48 @@ def test_non_finite_values_stay_in_their_subtree(case, op_dtype):
         keep[0, rows, 1, col] = False
         assert not np.any(np.isfinite(o[0, rows, 1, col]))
     assert np.array_equal(o[keep].view(np.uint32), clean[keep].view(np.uint32))
+
+
+@pytest.mark.parametrize("length", [9, 17, 32])  # the three widths of path registers
+def test_fp32_wy_products_keep_24_bits(length):
+    """A single term decides each output: one-hot keys and queries against the state (beta 0),
+    and against each other (state 0, value 1, each node its own index). The output is one
+    product of two fp32 numbers: at most 2^-24 of it is dropped by the three-part split, and
+    it is rounded by 2^-24 (the small partial products round 2^-7 times finer). The values
+    include the one that loses most when the first part is cut off (0x3f80ff80)."""
+    parents = [trees.chain(length), np.array([-1] + [0] * 40, np.int32)]
+    wl = _workload(parents, 2, 2, ops.F32)
+    rng = np.random.default_rng(55)
+    a = {k: np.zeros_like(x) for k, x in wl.arrays.items()}
+
+    def factor(shape):
+        x = (1 + rng.random(shape)).astype(np.float32)
+        x.flat[::3] = np.uint32(0x3F80FF80).view(np.float32)
+        return x
+
+    index = np.concatenate([np.arange(len(p)) for p in parents])
+    rows = np.concatenate([gu.node_rows(wl, r) for r in range(2)])
+    key, query = factor((2, len(rows), 2)), factor((2, len(rows), 2))
+    print(f"[gpu] fp32 wy single products, paths of {length}", flush=True)
+    for part in ("state", "gram"):
+        b = {k: x.copy() for k, x in a.items()}
+        for l in range(2):
+            for h in range(2):
+                b["q"][l, rows, h, index] = query[l, :, h]
+                b["k"][l, rows, h, index] = key[l, :, h]
+        if part == "state":
+            b["state0"][:] = factor(b["state0"].shape)
+            want = np.zeros((2, wl.total_rows, 2, 128))
+            for r in range(2):
+                at = slice(0, length) if r == 0 else slice(length, None)
+                for l in range(2):
+                    for h in range(2):
+                        want[l, rows[at], h] = (query[l, at, h].astype(np.float64)[:, None]
+                                                * b["state0"][r, l, h][index[at]].astype(np.float64))
+        else:
+            b["beta"][:], b["v"][:] = 1.0, 1.0
+            want = np.zeros((2, wl.total_rows, 2, 128))
+            want[:, rows] = (query.astype(np.float64) * key)[..., None]
+        o = _verify(wl, b)[:, rows]
+        want = want[:, rows]
+        assert np.max(np.abs(o - want) / np.abs(want)) <= 2.0 ** -23 + 2.0 ** -27, part
