@@ -242,6 +242,18 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
     // zero coefficient.
     uint64_t spoilt = 0;
 
+    // largest magnitude of z and x's entries, NaN if one is
+    auto largest = [](float z, const f32x4& x) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) z = __builtin_elementwise_maximum(z, __builtin_fabsf(x[i]));
+        return z;
+    };
+    // this lane's keys 32 kb + 8 lg + e of a row; finite entries of x, the others from y
+    auto whole_row = [&](const float* mat, int row) { return mat + ((krow0 + row) * p.h_k + hk) * kD + 8 * lg; };
+    auto keep_finite = [](f32x4& x, const f32x4& y) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[i] = __builtin_fabsf(x[i]) < INFINITY ? x[i] : y[i];
+    };
     // R0 [k | q] of the chunk's two halves of 16 nodes: x[hf][0], [1] the k products of column
     // tiles 0, 1, x[hf][2], [3] the q products; after the 4 x 4 exchange of lane groups
     // (permlane32, then permlane16 swaps) lane l < 32 holds in x[hf][b][i] R0 k, lane l + 32
@@ -311,6 +323,28 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
                 }
             }
             asm volatile("" ::: "memory");
+        }
+    };
+    // An infinite factor has no three parts (its remainder is NaN, and it meets zero and
+    // opposite parts of the other factor), and one next to the largest float rounds up to one:
+    // products of half hf that are not finite are taken again from the whole values, on the
+    // fp32 matrix instructions.
+    auto recheck = [&](int hf, int rowN, f32x4 (&x)[4]) {
+        float z = 0.f;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) z = largest(z, x[c]);
+        if (__ballot(!(z < INFINITY)) == 0) return;  // uniform
+        const int row = __shfl(rowN, 16 * hf + lq);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float* src = whole_row(c < 2 ? p.k : p.q, row);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int kb = 0; kb < kD / 32; ++kb)
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(src[32 * kb + e], R0[c & 1][kb][e], acc, 0, 0, 0);
+            keep_finite(x[c], acc);
         }
     };
     auto exchange = [&](f32x4 (&x)[4]) {
@@ -387,10 +421,36 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
                 }
                 asm volatile("" ::: "memory");
             }
+            float z = 0.f;
 #pragma unroll
             for (int i = 0; i < kRT; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) G[(16 * i + 4 * lg + e) * kGS + 16 * wave + lq] = small[i][e] + big[i][e];
+                for (int e = 0; e < 4; ++e) small[i][e] += big[i][e];
+#pragma unroll
+            for (int i = 0; i < kRT; ++i) z = largest(z, small[i]);
+            if (__ballot(!(z < INFINITY))) {  // uniform: as for R0 [k | q] (recheck)
+                const float* cs = whole_row(wave < 2 ? p.k : p.q, __shfl(rowN, (16 * wave + lq) % kTile));
+#pragma unroll
+                for (int i = 0; i < kRT; ++i) {
+                    int row = __shfl(rowN, (16 * i + kStack + lq) % kTile);  // a node of the chunk
+                    if (16 * i < kStack) {
+                        const int s = stacks[(c0 / kTile) * kStack + 16 * i + lq];
+                        row = s < 0 ? prow[c0] : s;
+                    }
+                    const float* rs = whole_row(p.k, row);
+                    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                    for (int kb = 0; kb < kD / 32; ++kb)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rs[32 * kb + e], cs[32 * kb + e], acc, 0, 0, 0);
+                    keep_finite(small[i], acc);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kRT; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) G[(16 * i + 4 * lg + e) * kGS + 16 * wave + lq] = small[i][e];
         }
         f32x4 px[2][4];
         products(two, px);
@@ -520,12 +580,14 @@ __global__ __launch_bounds__(kThr, 2) void wyf_kernel(WyfParams p) {
             }
         };
         load_values(0);
+        recheck(0, rowN, px[0]);
         exchange(px[0]);
         recursion(0, px[0]);
         if (two) {
             load_values(1);
             // the next chunk's rows, behind the values (only now are there registers for them)
             if (more) stage_load(rowC, stg);
+            recheck(1, rowN, px[1]);
             exchange(px[1]);
             recursion(1, px[1]);
         }

@@ -161,3 +161,73 @@ def test_fp32_wy_products_keep_24_bits(length):
         o = _verify(wl, b)[:, rows]
         want = want[:, rows]
         assert np.max(np.abs(o - want) / np.abs(want)) <= 2.0 ** -23 + 2.0 ** -27, part
+
+
+def _wy_form(q, k, v, g, beta, state, par):
+    """The WY form of one head in 64 bits, nodes in storage order (parents first)."""
+    path, out, delta = [], [], []
+    for t, p in enumerate(par):
+        anc = oracle.plan.ancestry(par, t)
+        gam = np.exp(sum(g[m] for m in anc))
+        d = beta[t] * (v[t] - gam * (k[t] @ state))
+        o = gam * (q[t] @ state)
+        for j, m in enumerate(anc[:-1]):
+            decay = np.exp(sum(g[x] for x in anc[j + 1:]))
+            d = d - (beta[t] * decay * (k[m] @ k[t])) * delta[m]
+            o = o + (decay * (k[m] @ q[t])) * delta[m]
+        delta.append(d)
+        out.append(o + (k[t] @ q[t]) * d)
+    return np.array(out)
+
+
+def _kind(x):
+    return np.where(np.isnan(x), 2, np.where(np.isinf(x), np.sign(x), 0))
+
+
+@pytest.mark.parametrize("case,op_dtype,where", [(c, ops.F32, w) for c in ("nine", "seventeen", "deep")
+                                                 for w in ("state0", "k", "q", "state0 k")]
+                         + [("deep", ops.BF16, w) for w in ("state0", "k", "q")])
+def test_infinities_pass_as_in_a_dot_product(case, op_dtype, where):
+    """An infinite entry of the state, a key or a query (and two of them that meet) gives the
+    outputs that whole fp32 factors give: the same infinities with the same sign, NaN only
+    where two of them meet, and finite values everywhere else. Values of every fourth node are
+    exact in bf16, so that an infinity meets zero parts. Finite outputs are held to the
+    parity tolerance per instance."""
+    wl = _workload(_trees(case), 1, 2, op_dtype)
+    a = {k: x.copy() for k, x in wl.arrays.items()}
+    f32 = op_dtype == ops.F32
+    for name in ("q", "k"):
+        if f32:
+            a[name][:, ::4] = ops.bf16_bits_to_f32(ops.to_bf16_bits(a[name][:, ::4]))
+    for r, par in enumerate(wl.parents):
+        rows = gu.node_rows(wl, r)
+        if len(par) < 4:
+            continue
+        if "state0" in where:
+            a["state0"][r, 0, 1, 3 + r, 40] = np.inf
+            a["state0"][r, 0, 1, 90, 41 + r] = -np.inf
+        for name in ("k", "q"):
+            if name in where:
+                for node, entry, neg in ((0, 60, False), (len(par) // 2, 17, False), (len(par) - 1, 3 + r, True)):
+                    x = -np.inf if neg else np.inf
+                    a[name][0, rows[node], 0, entry] = x if f32 else (0xFF80 if neg else 0x7F80)
+    print(f"[gpu] infinities {case} dtype={op_dtype} in {where}", flush=True)
+    o = _verify(wl, a)
+    val = {n: (x if x.dtype == np.float32 else ops.bf16_bits_to_f32(x)).astype(np.float64) for n, x in a.items()}
+    seen = set()
+    with np.errstate(all="ignore"):
+        for r, par in enumerate(wl.parents):
+            rows = gu.node_rows(wl, r)
+            for l in range(2):
+                for h in range(2):
+                    if len(par) == 0:
+                        continue
+                    ref = _wy_form(val["q"][l, rows, 0], val["k"][l, rows, 0], val["v"][l, rows, h], val["g"][l, rows, h],
+                                   val["beta"][l, rows, h], val["state0"][r, l, h], par)
+                    got = o[l, rows, h]
+                    assert np.array_equal(_kind(got), _kind(ref)), (r, l, h)
+                    seen |= set(np.unique(_kind(ref)).tolist())
+                    ok = np.isfinite(ref)
+                    tol = gu.TOL_F32 if f32 else gu.TOL_BF16
+                    assert np.max(np.abs(got - ref)[ok], initial=0.0) <= tol * np.max(np.abs(ref[ok]), initial=1e-30), (r, l, h)
+    assert len(seen) >= 3, seen
