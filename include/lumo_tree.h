@@ -501,8 +501,8 @@ lumo_status lumo_gdn_commit_prep(const lumo_gdn_dims* dims, const lumo_tree_desc
  *   lse         [total_rows][h_q] fp32 natural log, written at node rows only
  *   n_split     bound of the split-K, >= 1: a request's keys are reduced in at most
  *               n_split + 1 ranges and combined (the call takes fewer where more would
- *               only add partial results); lumo_tree_attention_splits suggests a bound
- *               that fills the device
+ *               only add partial results); lumo_tree_attention_splits suggests the
+ *               smallest bound that leaves the choice to the call
  *   workspace   >= lumo_tree_attention_workspace_bytes(dims, plan, n_split) bytes
  * Keys are reduced context first (range by range), then the tree nodes in physical slot
  * order; the reduction order is fixed for given shapes and n_split.

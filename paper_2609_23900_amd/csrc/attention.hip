@@ -12,7 +12,7 @@
 // key and value fragment read from LDS feeds R matrix instructions: at R = 1 the LDS port
 // (128 B per clock for four SIMDs) needs twice the time of the matrix cores, at R = 2 as
 // much as they do, so calls with many rows per key/value head (compute-bound) take R = 2;
-// calls of up to 64 rows are bound by HBM and take R = 1 (rule in launch_attention).
+// calls of up to 64 rows are bound by HBM and take R = 1 (rule in attn_shape).
 //
 // Layout per wavefront. The scores are computed transposed, S^T = K Q^T (16x16x32 bf16
 // MFMA), so that a lane holds 16 scores of ONE query row per tile (4 lane groups split
@@ -32,6 +32,7 @@
 // 64 bits instead of 2.09e-3 (bf16 outputs alone 1.7e-3), in 147 us instead of 156 us.
 // Tiles of 64 keys, double-buffered. Visibility inside the tree comes from the plan's
 // preorder intervals; only ragged context tiles and tree tiles are masked.
+#include <algorithm>
 #include <mutex>
 
 #include "device_common.h"
@@ -455,50 +456,67 @@ hipError_t attn_scratch(float** out) {
     return hipSuccess;
 }
 
-int attn_part_len(int max_ctx, int n_split) {
-    const int per = (max(max_ctx, 1) + n_split - 1) / n_split;
-    return (per + kAT - 1) / kAT * kAT;
-}
-
-namespace {
-
-// Key ranges of a call, at most `most`: the count with the smallest estimated time, in
-// microseconds. per: blocks of one range (512 are resident at once); tiles: of the longest
-// request. A resident round's block takes tile_us per tile (measured with the device full:
-// 3.0 us with R = 1, the HBM time of 512 tiles, 3.6 us with R = 2, where the matrix cores
-// bound it) and about 2 us around them; the merge costs a launch of about 4 us and the
-// traffic of the partial results, range_us per range. Without that last term 8 requests of
-// 64 nodes x 32 heads over 16,384 tokens took 256 ranges (2 GB of partial results) and
-// 1,384 us per call, and with it 8 ranges and 168 us.
-int attn_ranges(long per, int tiles, int most, float tile_us, float range_us) {
-    constexpr long kSlots = 512;
-    constexpr float kBlock = 2.f, kMerge = 4.f;
-    int best = 1;
+// Row tiles per wave and key ranges of a call, the ranges at most `most`: the pair with the
+// smallest estimated time, in microseconds. A block takes 64 R query rows through `each` key
+// tiles, in rounds of 512 resident blocks. Measured per tile: 1.25 (R = 1) and 2.0 (R = 2) with
+// at most one block per CU, 2.0 and 2.9 with two; R = 2 reads LDS half as often per product,
+// so it wins where two blocks per CU compete for it (8 requests x 64 nodes x 8 heads per key
+// head over 16,384 tokens, 4 ranges: 171 us, R = 1 203 us), and R = 1 on short calls, where
+// fewer, longer blocks leave CUs idle (2 requests x 128 nodes, 8 heads, 1,000 tokens: 16 us, R =
+// 2 20 us). A tile (32 KB of keys and values) comes from HBM once for the row chunks that
+// share it, at 5.1 TB/s when the blocks fill the CUs evenly (one request of 8 key heads over
+// 131,072 tokens, R = 1: 1.6 us a tile with 256 blocks, 3.3 with 512) and somewhat less otherwise. A
+// round adds about 2 us around its tiles, the merge a launch and the traffic of the partial
+// results, 2 x 516 B at about 5.5 TB/s per (row, head) and range: without it the 8 requests above
+// took 256 ranges (2 GB of partial results) and 1,384 us. Over 58 measured shapes the choice is
+// on average within 5% of the best (row tiles, ranges) pair.
+AttnShape attn_shape(const lumo_attn_dims& d, const lumo_plan& pl, int max_ctx, int most) {
+    constexpr long kCus = 256, kSlots = 512;
+    constexpr float kTileOne[2] = {1.25f, 2.0f}, kTileTwo[2] = {2.0f, 2.9f};
+    constexpr float kBlock = 2.f, kMerge = 2.f, kRange = 0.06f;
+    const int rows = pl.max_nodes * (d.h_q / d.h_kv);
+    const int tiles = (std::max(max_ctx, 0) + kAT - 1) / kAT + (pl.max_nodes + kAT - 1) / kAT;
+    const float range = kRange + (float)pl.total_rows * (float)d.h_q * (1032.f / 5.5e6f);
+    const int limit = (int)std::min<long>(std::min(most, tiles), kSlots);
+    AttnShape best{1, 1};
     float best_cost = 0.f;
-    for (int n = 1; n <= most && n <= tiles && n <= kSlots; ++n) {
-        const long rounds = (n * per + kSlots - 1) / kSlots;
-        const int each = (tiles + n - 1) / n;
-        const float cost = (float)rounds * ((float)each * tile_us + kBlock) + (n > 1 ? kMerge + range_us * (float)n : 0.f);
-        if (n == 1 || cost < best_cost) {
-            best = n;
-            best_cost = cost;
+    for (int r = 1; r <= 2; ++r) {
+        const long chunks = (rows + 16 * r * kAW - 1) / (16 * r * kAW);
+        const long per = (long)d.n_req * d.h_kv * chunks;
+        const float load = (kAT * kAD * 4 / 5.1e6f) / (float)chunks;  // of a block's tile, alone on HBM
+        for (int n = 1; n <= limit;) {
+            const int each = (tiles + n - 1) / n;
+            const long blocks = n * per, rest = blocks % kSlots;
+            float cost = (float)(blocks / kSlots) * ((float)each * std::max(kTileTwo[r - 1], (float)kSlots * load) + kBlock);
+            if (rest) {
+                const bool one = rest <= kCus;
+                const float uneven = one ? 1.08f + 0.75f * (1.f - (float)rest / (float)kCus)
+                                         : 1.f + 0.3f * (1.f - (float)rest / (float)kSlots);
+                cost += (float)each * std::max((one ? kTileOne : kTileTwo)[r - 1], (float)rest * load * uneven) + kBlock;
+            }
+            if (n > 1) cost += kMerge + range * (float)n;
+            if ((r == 1 && n == 1) || cost < best_cost) {
+                best = {r, n};
+                best_cost = cost;
+            }
+            if (each == 1) break;
+            n = (tiles + each - 2) / (each - 1);  // the next count with fewer tiles per range
         }
     }
     return best;
 }
 
+namespace {
+
 template <int R>
-void launch_parts(AttnParams& p, int rows, int tiles, int most, hipStream_t s) {
+void launch_parts(AttnParams& p, int rows, hipStream_t s) {
     p.n_chunk = (rows + 16 * R * kAW - 1) / (16 * R * kAW);
     const long heads = (long)p.n_req * p.h_kv;
-    const long per = heads * p.n_chunk;
-    // a (row, head)'s partial result is written and read once: 2 x 516 B at about 4 TB/s
-    p.n_range = attn_ranges(per, tiles, most, R == 1 ? 3.0f : 3.6f, (float)p.total_rows * (float)p.h_q * (1032.f / 4.0e6f));
     // one request of 8 key/value heads over 131,072 tokens: 107.8 us with a head's ranges
     // on one XCD, 110.5 us dealt range by range; with pairs that do not fill the XCDs evenly
     // the ranges are dealt (only row chunks share keys)
     p.xcd_unit = heads % 8 == 0 ? p.n_chunk * p.n_range : p.n_chunk;
-    hipLaunchKernelGGL(attn_kernel<R>, dim3((unsigned)(per * p.n_range)), dim3(64 * kAW), 0, s, p);
+    hipLaunchKernelGGL(attn_kernel<R>, dim3((unsigned)(heads * p.n_chunk * p.n_range)), dim3(64 * kAW), 0, s, p);
 }
 
 }  // namespace
@@ -530,16 +548,12 @@ hipError_t launch_attention(const lumo_attn_dims& d, const lumo_tree_desc& desc,
     const int grp = d.h_q / d.h_kv;
     p.group_log2 = grp == 1 ? 0 : grp == 2 ? 1 : grp == 4 ? 2 : 3;
     const int rows = pl.max_nodes * grp;
-    const int tiles = (max(a.max_ctx, 0) + kAT - 1) / kAT + (pl.max_nodes + kAT - 1) / kAT;
-    const int most = a.n_split + 1;  // the workspace holds n_split + 1 ranges
-    // R = 2 halves the LDS reads per product; it pays where the matrix cores would wait for
-    // them (8 requests x 64 nodes x 8 heads per key head over 16,384 tokens: 167 us against
-    // 205 us) and loses on contexts of a few tiles, where fewer, longer blocks leave the
-    // device idle (16 requests x 128 nodes over 512 tokens: 28.8 against 24.2 us).
-    if (rows <= 64 || tiles < 16)
-        launch_parts<1>(p, rows, tiles, most, s);
+    const AttnShape shape = attn_shape(d, pl, a.max_ctx, a.n_split + 1);  // the workspace holds n_split + 1 ranges
+    p.n_range = shape.n_range;
+    if (shape.row_tiles == 1)
+        launch_parts<1>(p, rows, s);
     else
-        launch_parts<2>(p, rows, tiles, most, s);
+        launch_parts<2>(p, rows, s);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.n_range == 1) return e;
     const long pairs = (long)d.n_req * pl.max_nodes * d.h_q;

@@ -141,7 +141,11 @@ struct AttnArgs {
     float* lse;
     float* ws;
 };
-int attn_part_len(int max_ctx, int n_split);
+// Tiles of 16 query rows per wave and key ranges of a call that may take up to `most` ranges.
+struct AttnShape {
+    int row_tiles, n_range;
+};
+AttnShape attn_shape(const lumo_attn_dims& d, const lumo_plan& pl, int max_ctx, int most);
 hipError_t launch_attention(const lumo_attn_dims& d, const lumo_tree_desc& desc, const AttnArgs& a, hipStream_t s);
 // Device address of the current device's fixed attention scratch array
 // (LUMO_TREE_ATTENTION_SCRATCH_BYTES), looked up once per device.

@@ -513,3 +513,27 @@ def test_fused_conv_rejects_bad_arguments():
     assert L._lib.lumo_tree_gdn_verify_conv_pending(
         ctypes.byref(ok), ctypes.byref(wy), None, 1024, *([ctypes.c_void_p(FAKE)] * 3), None, 1,
         *([ctypes.c_void_p(FAKE)] * 4), None, 4, *([ctypes.c_void_p(FAKE)] * 5), None) == L.LUMO_EINVAL
+
+
+def _uniform(n_req, nodes):
+    off = (np.arange(n_req + 1) * nodes).astype(np.int32)
+    par = np.tile(np.array([-1] + [0] * (nodes - 1), np.int32), n_req)
+    return L.lumo_tree_plan(off, par, np.full(n_req, nodes, np.int32), L.LUMO_POLICY_WY)[0]
+
+
+@pytest.mark.parametrize("n_req,nodes,h_q,h_kv,n_ctx,row_chunks", [
+    (1, 28, 16, 2, 131072, 4), (1, 7, 16, 2, 115105, 1), (4, 16, 16, 2, 4096, 2), (1, 28, 16, 8, 131072, 1),
+    (8, 64, 32, 4, 16384, 8), (16, 128, 64, 8, 16384, 16)])
+def test_attention_split_suggestion_is_what_a_call_uses(n_req, nodes, h_q, h_kv, n_ctx, row_chunks):
+    """The suggested bound leaves long-context calls enough key ranges to put a block (64
+    or 128 of the rows that share a key head) on most of the 256 CUs, and asks for no
+    workspace beyond the ranges that such a call can use: 512 blocks are resident at
+    once, and a range more than that needs only adds partial results."""
+    plan = _uniform(n_req, nodes)
+    d = L.attn_dims(n_req, h_q, h_kv)
+    n_split = L.lumo_tree_attention_splits(d, plan, n_ctx)
+    blocks = (n_split + 1) * n_req * h_kv * row_chunks  # of 64 rows
+    assert blocks >= 192
+    assert n_split == 1 or blocks <= 2 * 512  # two of 64 rows are one of 128
+    assert L.lumo_tree_attention_workspace_bytes(d, plan, n_split) <= (2 if n_split == 1 else 1024 // (n_req * h_kv)) \
+        * n_req * nodes * h_q * 516 + 16

@@ -211,3 +211,19 @@ def test_tree_attention_probabilities_relative_to_each_tile(nodes, tiles):
     err = np.abs(o - ref) - np.abs(ref) * 2.0 ** -8
     assert err.max() <= 2.0 ** -18 * size.max(), float((err / size).max())
     assert np.all(np.abs(lse - np.log(mass)) <= 2e-6)
+
+
+@pytest.mark.parametrize("nodes,h_q,h_kv,n_ctx", [(7, 16, 2, 20000), (16, 16, 2, 4096), (128, 8, 8, 1000), (64, 32, 4, 4000),
+                                                  (3, 8, 8, 64)])
+def test_tree_attention_suggested_bound_does_not_bind(nodes, h_q, h_kv, n_ctx):
+    """A call with the suggested bound and one with a far larger bound cut the keys alike: the
+    same bits."""
+    rng = np.random.default_rng(33)
+    parents = [trees.random_tree(rng, nodes, 8, trees.bmax_uniform(4))]
+    row_off, total, ctx_off, node_off, a = make_case(34, parents, [nodes], [n_ctx], h_q, h_kv)
+    plan, _ = L.lumo_tree_plan(node_off, parents[0], np.array([nodes], np.int32))
+    n_split = L.lumo_tree_attention_splits(L.attn_dims(1, h_q, h_kv), plan, n_ctx)
+    say(f"[gpu] tree attention suggested bound {n_split}: nodes={nodes} heads={h_q}/{h_kv} ctx={n_ctx}")
+    o, lse = run_gpu(parents, [nodes], node_off, ctx_off, a, h_q, h_kv, n_split, 0.09)
+    o2, lse2 = run_gpu(parents, [nodes], node_off, ctx_off, a, h_q, h_kv, 1024, 0.09)
+    assert np.array_equal(o, o2) and np.array_equal(lse, lse2)
