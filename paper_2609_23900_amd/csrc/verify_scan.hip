@@ -15,6 +15,7 @@
 // IV-B) the gates come from raw inputs and the key and query rows are used divided by
 // sqrt(|x|^2 + eps), computed as the commit's replay computes them.
 #include "device_common.h"
+#include "dispatch.h"
 #include "internal.h"
 #include "launch.h"
 
@@ -318,19 +319,12 @@ hipError_t launch_tree(int dk, const ScanTreeParams& p, long nb, hipStream_t s, 
 }
 
 // Whether scan_tree_kernel takes a call: plans that carry the traversal and need at most
-// kScanSlots saved states, without node-state dump or operand preparation. It is the faster
-// form of PATHS and TWO_LEVEL at every size measured (8 requests x 6 layers x 64 nodes,
-// 32 heads, d = 128: 1,175 -> 280 us; one request, one layer, 64 nodes: 83 -> 38 us).
-// RECOMPUTE runs every root-to-leaf path side by side, so a call too small to fill the
-// device takes the depth of its trees (about 3.3 us a level) instead of their nodes
-// (0.55 us each): one request, one layer, 64 nodes of 8 levels 26.7 us against 37.5 us; with
-// 1,024 column tiles (4 requests of 150 nodes) it is 209 us against 95 us.
+// kScanSlots saved states, without node-state dump or operand preparation, where it is the
+// faster form (8 requests x 6 layers x 64 nodes, 32 heads, d = 128: 1,175 -> 280 us; small
+// calls with wide trees are not: scan_tree_faster).
 bool scan_tree_takes(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, int64_t section) {
-    const lumo_plan& pl = desc.plan;
     if (section < 0 || desc.host_blob[section] > kScanSlots || a.node_states || a.prep.flags != 0) return false;
-    if (pl.policy != LUMO_POLICY_RECOMPUTE) return true;
-    const long tiles = (long)d.n_req * d.n_layers * d.h_v * (d.d_v / 16);
-    return tiles > 256 || pl.max_nodes <= 6 * pl.max_depth;
+    return scan_tree_faster(d, desc.plan, desc.host_blob);
 }
 
 template <int DK, int OPT>

@@ -1,0 +1,79 @@
+"""The host rules that choose between two forms of a kernel (csrc/dispatch.h), compiled with the
+host compiler and evaluated on plans: the form that was measured faster is the one taken."""
+from __future__ import annotations
+
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+import paper_2609_23900_amd as L
+from lumo_synth import trees
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def rules(tmp_path_factory):
+    d = tmp_path_factory.mktemp("rules")
+    src = d / "rules.cpp"
+    src.write_text('''#include "dispatch.h"
+extern "C" int scan_tree(const lumo_gdn_dims* d, const lumo_plan* p, const int32_t* b) {
+    return lumo::scan_tree_faster(*d, *p, b);
+}
+''')
+    lib = d / "rules.so"
+    subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I",
+                    os.path.join(ROOT, "paper_2609_23900_amd", "csrc"), str(src), "-o", str(lib)], check=True)
+    return ctypes.CDLL(str(lib))
+
+
+def _plan(parents, policy):
+    off = np.concatenate([[0], np.cumsum([len(p) for p in parents])]).astype(np.int32)
+    return L.lumo_tree_plan(off, np.concatenate(parents).astype(np.int32), np.diff(off).astype(np.int32), L.POLICIES[policy])
+
+
+def _star(n):
+    return np.array([-1] + [0] * (n - 1), np.int32)
+
+
+def _levels(n, levels):
+    return trees.random_tree(np.random.default_rng(5), n, levels, trees.bmax_uniform(4))
+
+
+ONE = (1, 16, 32, 128, 128)  # one layer of 16 key and 32 value heads
+
+
+@pytest.mark.parametrize("policy,tree,n_req,shape,single", [
+    # measured at both forms: level by level first, then the single launch, us
+    ("two_level", _star(256), 1, ONE, 0),          # 47, 143
+    ("paths", _star(256), 1, ONE, 0),              # 48, 142
+    ("paths", _star(64), 2, ONE, 0),               # 32, 40
+    ("recompute", _star(256), 2, ONE, 0),          # 90, 144
+    ("two_level", _levels(256, 8), 1, ONE, 0),     # 109, 143
+    ("recompute", _levels(64, 8), 1, ONE, 0),      # 30, 37
+    ("two_level", _levels(64, 8), 8, (2, 2, 4, 32, 128), 0),   # 18, 35
+    ("two_level", _levels(200, 16), 8, (2, 4, 4, 16, 16), 0),  # 24, 46
+    ("paths", _levels(256, 8), 1, ONE, 1),         # 178, 143
+    ("paths", _levels(64, 8), 1, ONE, 1),          # 99, 39
+    ("two_level", _levels(64, 8), 2, ONE, 1),      # 57, 39
+    ("recompute", trees.chain(64), 1, ONE, 1),     # 153, 36
+    ("paths", _star(256), 8, ONE, 1),              # 269, 167
+    ("two_level", _levels(64, 8), 8, (2, 8, 8, 128, 16), 1),   # 43, 37
+    ("two_level", _star(100), 64, (1, 16, 32, 64, 64), 1),     # beyond 1,024 column tiles
+])
+def test_scan_form_is_the_faster_one(rules, policy, tree, n_req, shape, single):
+    plan, blob = _plan([tree] * n_req, policy)
+    layers, h_k, h_v, d_k, d_v = shape
+    d = L.dims(n_req, layers, h_k, h_v, d_k, d_v, L.LUMO_BF16)
+    assert rules.scan_tree(ctypes.byref(d), ctypes.byref(plan), L._hptr(blob)) == single
+
+
+def test_scan_rule_takes_empty_and_tiny_plans(rules):
+    for parents in ([np.zeros(0, np.int32)], [trees.chain(1), np.zeros(0, np.int32)]):
+        for policy in ("paths", "two_level", "recompute"):
+            plan, blob = _plan(parents, policy)
+            d = L.dims(len(parents), 1, 1, 1, 16, 16, L.LUMO_F32)
+            assert rules.scan_tree(ctypes.byref(d), ctypes.byref(plan), L._hptr(blob)) in (0, 1)

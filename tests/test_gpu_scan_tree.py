@@ -1,7 +1,8 @@
 """The sequential policies' single-launch scan against the level-by-level scan, bit for bit.
 
 A call that asks for the node states runs level by level; the same call without them
-takes the single launch. Both must leave the same output bits at every node row and touch
+takes the single launch (the layers are chosen so that it does at any tree: more than 1,024
+column tiles, below which calls with wide trees stay level by level). Both must leave the same output bits at every node row and touch
 no pad row, for every key and value dimension, both operand types, grouped heads, trees that
 end on and around the 16-node chunks, zero to four saved states, and trees that need more
 (which stay level by level).
@@ -51,7 +52,7 @@ def test_single_launch_scan_equals_level_by_level(tree, dtype, h_k, h_v, d_k, d_
     parents = TREES[tree](rng)
     n_rows = np.array([len(p) + 1 + i % 2 for i, p in enumerate(parents)], np.int32)
     node_off = np.concatenate([[0], np.cumsum([len(p) for p in parents])]).astype(np.int32)
-    n_layers, rows = 2, int(n_rows.sum())
+    n_layers, rows = 1024 // (len(parents) * h_v * (d_v // 16)) + 1, int(n_rows.sum())
     a = ops.make_gdn_operands(7, n_req=len(parents), n_layers=n_layers, total_rows=rows, h_k=h_k, h_v=h_v, d_k=d_k,
                               d_v=d_v, op_dtype=dtype)
     bf = dtype == ops.BF16
