@@ -10,6 +10,7 @@
 // follow it closely in each request's depth-first preorder, so most re-reads hit L2).
 // HBM-bound.
 #include "device_common.h"
+#include "dispatch.h"
 #include "internal.h"
 #include "launch.h"
 
@@ -247,7 +248,7 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvParams p) {
 // arithmetic is conv_kernel's (the same bits). Bound by HBM: conv_kernel loads every window
 // row from L2 and re-reads x 1.4 to 1.6 times from HBM; this walk reads it once, and a few
 // rows per run again. One-wave blocks, so that a run's serial walk waits for nobody; the
-// grid must hold enough of them (rule and figures in launch_conv). kG: rows loaded ahead.
+// grid must hold enough of them (conv_walk in dispatch.h). kG: rows loaded ahead.
 template <int OPT, int kG>
 __global__ __launch_bounds__(64) void conv_walk_kernel(ConvParams p) {
     using T = typename Op<OPT>::T;
@@ -632,20 +633,12 @@ hipError_t launch_conv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const
     p.y = a.y;
     p.o_pre_row = pl.o_pre_row;
     p.o_pre_depth = pl.o_pre_depth;
-    // The walk over runs, where the grid holds at least 2,048 of its one-wave blocks (eight per
-    // CU) and a root path fits in 20 KB of LDS (eight blocks per CU). fp32 operands take runs
-    // of 16 nodes: 8 requests x 12 layers x 64 nodes x 8,192 channels 125 -> 82 us, 3 layers
-    // 22.9 -> 18.2 us; below the line 11.8 against 11.3 us, paths of 32 nodes 22.9 against 26.9.
-    // bf16 rows are half as long, so a run has to be longer to pay for its start: 64
-    // nodes, with rows loaded eight ahead (32 requests x 256 nodes 69 -> 57 us; 64 requests
-    // of 16 and 128 nodes, below the line, 36 against 49 us).
-    const bool bf = d.op_dtype == LUMO_BF16;
-    const int run_nodes = bf ? 64 : 16, lane_channels = bf ? 8 : 4;
-    const int walk_chunks = (a.channels + 64 * lane_channels - 1) / (64 * lane_channels);
-    if (pl.max_depth + 3 <= 20 && (long)pl.total_nodes / run_nodes * d.n_layers * walk_chunks >= 2048) {
-        p.run = run_nodes;
+    const ConvWalk walk = conv_walk(d, pl, desc.host_blob, a.channels);
+    if (walk.run_nodes) {
+        const bool bf = d.op_dtype == LUMO_BF16;
+        p.run = walk.run_nodes;
         p.n_runs = (pl.max_nodes + p.run - 1) / p.run;
-        p.n_cchunks = walk_chunks;
+        p.n_cchunks = (a.channels + 64 * walk.lane_channels - 1) / (64 * walk.lane_channels);
         const long nb = (long)p.n_runs * p.n_cchunks * d.n_req * d.n_layers;
         const size_t lds = (size_t)(pl.max_depth + 3) * 64 * sizeof(uint4);
         if (bf)

@@ -40,4 +40,55 @@ inline bool scan_tree_faster(const lumo_gdn_dims& d, const lumo_plan& p, const i
     return level >= tree;
 }
 
+// The conv's walk over runs (conv.hip): nodes per run and channels per lane, 0 nodes where the
+// run kernel is faster. A run starts by loading its ancestors and weights, and the grid has
+// as many runs for every request as the largest one needs. So the walk takes calls
+//  - of at least 2,048 blocks' work (eight one-wave blocks per CU), with root paths that
+//    leave LDS for eight blocks per CU (20 KB);
+//  - whose runs, where a request has several, are mostly full: six tenths in fp32 (32 requests x
+//    33 nodes, 4 layers x 8,192 channels: run kernel 84, walk 63 us; 128 requests x 17 nodes, 2
+//    layers: 88 and 99 us), three quarters in bf16 (32 x 96 nodes, 4 layers: 111 and 113
+//    us; 64 x 65 nodes, 2 layers: 77 and 96 us);
+//  - with enough of the blocks in use: a fifth in fp32, where they are short (256 and 31 x 32
+//    nodes, 2 layers x 8,192 channels: 35 and 48 us), half in bf16 (4 requests x 512 and 28 x
+//    64 nodes, 4 layers x 8,192: 135 and 232 us; 16 requests of 256 and 32 nodes in turn: 92
+//    and 95 us);
+//  - whose work is spread over the XCDs, each of which takes an eighth of the layers' requests in
+//    order: the busiest at most 1.5 times the average (4 requests x 512 and 28 x 64 nodes, fp32, 1
+//    layer x 8,192: 4.3 times, 48 and 131 us; 4 layers: 1.47 times, 303 and 298 us; 6
+//    layers x 2,304: 168 and 112 us. Dealt over the XCDs instead, requests of 256 and 32
+//    nodes in turn took 1.4 times as long).
+// fp32 operands take runs of 16 nodes: 8 requests x 12 layers x 64 nodes x 8,192 channels 125 ->
+// 82 us, 3 layers 22.9 -> 18.2 us; below the line 11.8 against 11.3 us, paths of 32 nodes 22.9
+// against 26.9. bf16 rows are half as long, so a run has to be longer to pay for its start:
+// 64 nodes (32 requests x 256 nodes 69 -> 57 us).
+struct ConvWalk {
+    int run_nodes, lane_channels;
+};
+inline ConvWalk conv_walk(const lumo_gdn_dims& d, const lumo_plan& p, const int32_t* host_blob, int channels) {
+    const bool bf = d.op_dtype == LUMO_BF16;
+    const ConvWalk walk{bf ? 64 : 16, bf ? 8 : 4}, none{0, 0};
+    const int64_t chunks = (channels + 64 * walk.lane_channels - 1) / (64 * walk.lane_channels);
+    if (p.max_depth + 3 > 20 || (int64_t)p.total_nodes / walk.run_nodes * d.n_layers * chunks < 2048) return none;
+    const int64_t most = (p.max_nodes + walk.run_nodes - 1) / walk.run_nodes;
+    int64_t runs = 0;
+    for (int r = 0; r < d.n_req; ++r) {
+        const int n = host_blob[p.o_node_off + r + 1] - host_blob[p.o_node_off + r];
+        runs += (n + walk.run_nodes - 1) / walk.run_nodes;
+    }
+    if (most > 1 && 20 * (int64_t)p.total_nodes < (bf ? 15 : 12) * walk.run_nodes * runs) return none;
+    if ((bf ? 2 : 5) * runs < d.n_req * most) return none;
+    // nodes of the layers' requests before position x / 8
+    const int64_t total = p.total_nodes;
+    auto before = [&](int64_t x) {
+        const int64_t i = x / 8, r = i % d.n_req;
+        const int32_t* off = host_blob + p.o_node_off + r;
+        return 8 * (i / d.n_req * total + off[0]) + x % 8 * (int64_t)(off[1] - off[0]);
+    };
+    const int64_t per = (int64_t)d.n_req * d.n_layers;
+    for (int k = 0; k < 8; ++k)
+        if (2 * (before((k + 1) * per) - before(k * per)) > 3 * d.n_layers * total) return none;
+    return walk;
+}
+
 }  // namespace lumo

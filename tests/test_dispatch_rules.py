@@ -23,6 +23,9 @@ def rules(tmp_path_factory):
 extern "C" int scan_tree(const lumo_gdn_dims* d, const lumo_plan* p, const int32_t* b) {
     return lumo::scan_tree_faster(*d, *p, b);
 }
+extern "C" int conv_run(const lumo_gdn_dims* d, const lumo_plan* p, const int32_t* b, int channels) {
+    return lumo::conv_walk(*d, *p, b, channels).run_nodes;
+}
 ''')
     lib = d / "rules.so"
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I",
@@ -77,3 +80,39 @@ def test_scan_rule_takes_empty_and_tiny_plans(rules):
             plan, blob = _plan(parents, policy)
             d = L.dims(len(parents), 1, 1, 1, 16, 16, L.LUMO_F32)
             assert rules.scan_tree(ctypes.byref(d), ctypes.byref(plan), L._hptr(blob)) in (0, 1)
+
+
+@pytest.mark.parametrize("sizes,bf16,layers,channels,run", [
+    ([2048] + [8] * 31, False, 1, 8192, 0),       # run kernel 36 us, walk 157
+    ([2048] + [8] * 31, True, 4, 8192, 0),        # 93, 130
+    ([65] * 64, True, 2, 8192, 0),                # 77, 96
+    ([17] * 128, False, 2, 8192, 0),              # 88, 99
+    ([65] * 64, False, 1, 8192, 16),              # 76, 60
+    ([64] * 8, False, 12, 8192, 16),              # 125, 82
+    ([64] * 8, False, 1, 8192, 0),                # too few blocks
+    ([256] * 32, True, 1, 8192, 64),              # 64, 56
+    ([16, 128] * 32, True, 2, 8192, 64),          # 93, 91
+    ([16, 128] * 32, False, 1, 8192, 16),         # 96, 85
+    ([28] * 64, False, 3, 8192, 16),              # 110, 76
+    ([33] * 32, False, 4, 8192, 16),              # 84, 63
+    ([512] * 4 + [64] * 28, False, 6, 2304, 16),  # 168, 112
+    ([512] * 4 + [64] * 28, True, 4, 8192, 0),    # 135, 232
+    ([256] + [32] * 31, False, 2, 8192, 0),       # 35, 48
+    ([256, 32] * 8, False, 2, 8192, 16),          # 96, 74
+    ([512] * 4 + [64] * 28, False, 1, 8192, 0),   # 48, 131: an XCD takes all the large trees
+    ([64] * 28 + [512] * 4, False, 2, 8192, 0),
+    ([512] * 4 + [64] * 28, False, 4, 8192, 16),  # 303, 298
+    ([512], False, 8, 8192, 16),                  # one request is spread by its channels
+])
+def test_conv_walk_is_taken_where_it_is_faster(rules, sizes, bf16, layers, channels, run):
+    rng = np.random.default_rng(9)
+    parents = [trees.random_tree(rng, n, 17, trees.bmax_uniform(4)) if n > 17 else trees.chain(n) for n in sizes]
+    plan, blob = _plan(parents, "recompute")
+    d = L.dims(len(sizes), layers, 1, 1, 128, 128, L.LUMO_BF16 if bf16 else L.LUMO_F32)
+    assert rules.conv_run(ctypes.byref(d), ctypes.byref(plan), L._hptr(blob), channels) == run
+
+
+def test_conv_walk_refuses_long_paths(rules):
+    plan, blob = _plan([trees.chain(18)] * 64, "recompute")
+    d = L.dims(64, 48, 1, 1, 128, 128, L.LUMO_F32)
+    assert rules.conv_run(ctypes.byref(d), ctypes.byref(plan), L._hptr(blob), 8192) == 0

@@ -25,7 +25,8 @@ from lumo_synth import trees  # noqa: E402
                                                                  (True, 4104, 24, 1, False), (True, 4096, 24, 0, True)])
 def test_walk_equals_run_kernel(bf16, channels, n_layers, act, with_bias):
     rng = np.random.default_rng(61)
-    sizes = (1, 15, 16, 17, 0, 33, 63, 64, 65, 128, 129, 200)
+    # full trees beside the edge sizes: the walk is for batches whose runs are mostly full
+    sizes = (1, 15, 16, 17, 0, 33, 63, 64, 65, 128, 129, 200) + (256,) * 8
     parents = [trees.random_tree(rng, n, 17, trees.bmax_uniform(2 + i % 3)) if n > 1 else trees.chain(n)
                for i, n in enumerate(sizes)] + [trees.chain(17)]
     n_rows = np.array([len(p) + 1 for p in parents], np.int32)
@@ -33,7 +34,9 @@ def test_walk_equals_run_kernel(bf16, channels, n_layers, act, with_bias):
     row_off = np.concatenate([[0], np.cumsum(n_rows)])
     nodes, rows, n_req = int(node_off[-1]), int(row_off[-1]), len(parents)
     per, lane = (64, 8) if bf16 else (16, 4)
-    assert nodes // per * n_layers * -(-channels // (64 * lane)) >= 2048  # the walk's line
+    runs = sum(-(-len(p) // per) for p in parents)  # the walk's lines
+    assert nodes // per * n_layers * -(-channels // (64 * lane)) >= 2048
+    assert 4 * nodes >= 3 * per * runs and 2 * runs >= n_req * -(-256 // per)
     dt = torch.bfloat16 if bf16 else torch.float32
     g = torch.Generator(device="cuda").manual_seed(62)
 
