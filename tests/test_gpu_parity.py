@@ -380,10 +380,12 @@ def test_wy_parity(name, n_inst):
     gu.check_states(wl, st.state.cpu().numpy(), ref_state, gu.sample_instances(wl, n_inst, seed=12))
 
 
-# ---------------------------------------------------------------- WY form on the vector ALUs
+# ------------------------------------------ WY form beyond the bf16 kernel for short paths
 
 def _wyv_case(case):
-    """Shapes the matrix-core kernel does not take, served by the vector-ALU WY kernel."""
+    """Shapes the bf16 matrix-core kernel for paths of up to 17 nodes does not take: fp32 at d =
+    128 and bf16 paths of up to 32 nodes have matrix-core kernels of their own, heads
+    below 128 run on the vector ALUs (more of those: test_gpu_wyv.py)."""
     rng = np.random.default_rng(91)
     if case == "tiny_f32":
         return configs.build("tiny", with_conv=False), [(0, 0, 0)]
@@ -414,8 +416,7 @@ def _wyv_case(case):
 
 @pytest.mark.parametrize("case", ["tiny_f32", "layer1_f32", "deep_bf16", "d64_group4_bf16", "d32_v16_f32"])
 def test_wyv_parity(case):
-    """The WY policy on shapes outside the matrix-core kernel (fp32 operands, d < 128,
-    paths beyond 17 nodes): outputs against the oracle, NaN pad rows neither read nor
+    """The WY policy on fp32 operands, d < 128 and paths beyond 17 nodes: outputs against the oracle, NaN pad rows neither read nor
     written, and the sequential scan of the same plan shape within the output tolerance."""
     wl, inst = _wyv_case(case)
     rows = set(oracle.plan.flat_rows(wl.parents, wl.row_off).tolist())
@@ -428,7 +429,7 @@ def test_wyv_parity(case):
     for key in ("g", "beta"):
         a[key] = a[key].copy()
         a[key][:, pad] = np.nan
-    say(f"[gpu] wyv {case}")
+    say(f"[gpu] wy {case}")
     st = run(wl, L.LUMO_POLICY_WY, with_conv=False, commit=False, arrays=a)
     o = gu.to_np(st.o)
     worst = gu.check_outputs(wl, o, inst, arrays=a)
@@ -444,7 +445,7 @@ def test_wyv_parity(case):
 
 
 def test_wyv_prep_parity():
-    """Operand preparation (Sec. IV-B) on the vector-ALU WY kernel: fp32 operands."""
+    """Operand preparation (Sec. IV-B) in the WY kernel of fp32 operands at d = 128."""
     wl, inst = _wyv_case("layer1_f32")
     rng = np.random.default_rng(93)
     a = dict(wl.arrays)
@@ -461,7 +462,7 @@ def test_wyv_prep_parity():
     st.verify()
     torch.cuda.synchronize()
     worst = _check_prep_outputs(wl, gu.to_np(st.o), a, oprep, inst, tol=gu.TOL_F32)
-    say(f"[gpu] wyv prep: outputs worst max-rel {worst:.3e}")
+    say(f"[gpu] wy fp32 prep: outputs worst max-rel {worst:.3e}")
 
 
 def test_wy_agrees_with_sequential_scan():
