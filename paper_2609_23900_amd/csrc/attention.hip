@@ -458,7 +458,7 @@ hipError_t attn_scratch(float** out) {
 
 // Row tiles per wave and key ranges of a call, the ranges at most `most`: the pair with the
 // smallest estimated time, in microseconds. A block takes 64 R query rows through `each` key
-// tiles, in rounds of 512 resident blocks. Measured per tile: 1.25 (R = 1) and 2.0 (R = 2) with
+// tiles, in rounds of 512 resident blocks. Measured per tile: 1.35 (R = 1) and 2.1 (R = 2) with
 // at most one block per CU, 2.0 and 2.9 with two; R = 2 reads LDS half as often per product,
 // so it wins where two blocks per CU compete for it (8 requests x 64 nodes x 8 heads per key
 // head over 16,384 tokens, 4 ranges: 171 us, R = 1 203 us), and R = 1 on short calls, where
@@ -472,7 +472,7 @@ hipError_t attn_scratch(float** out) {
 // on average within 5% of the best (row tiles, ranges) pair.
 AttnShape attn_shape(const lumo_attn_dims& d, const lumo_plan& pl, int max_ctx, int most) {
     constexpr long kCus = 256, kSlots = 512;
-    constexpr float kTileOne[2] = {1.25f, 2.0f}, kTileTwo[2] = {2.0f, 2.9f};
+    constexpr float kTileOne[2] = {1.35f, 2.1f}, kTileTwo[2] = {2.0f, 2.9f};
     constexpr float kBlock = 2.f, kMerge = 2.f, kRange = 0.06f;
     const int rows = pl.max_nodes * (d.h_q / d.h_kv);
     const int tiles = (std::max(max_ctx, 0) + kAT - 1) / kAT + (pl.max_nodes + kAT - 1) / kAT;
