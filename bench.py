@@ -47,7 +47,7 @@ TRAFFIC_RECORD = os.path.join(ROOT, "profiles", "traffic.json")
 # sources that determine the code of each policy's verify kernels
 VERIFY_SOURCES = {
     "wy": ["verify_wy.hip", "verify_wy_body.inc", "verify_wy.h", "device_common.h", "internal.h", "launch.h"],
-    "paths": ["verify_scan.hip", "device_common.h", "internal.h", "launch.h"],
+    "paths": ["verify_scan.hip", "dispatch.h", "device_common.h", "internal.h", "launch.h"],
     "wyf": ["verify_wyf.hip", "device_common.h", "internal.h", "launch.h"],
     "wyv": ["verify_wyv.hip", "device_common.h", "internal.h", "launch.h"],
     "attention": ["attention.hip", "device_common.h", "internal.h", "launch.h"],

@@ -75,9 +75,10 @@ typedef enum {
     /* Dependent path groups: the tree is cut into disjoint first-child chains; a
      * chain starts from the pre-tree state (the spine) or from the cut state of its
      * parent; each node is updated once. Needs a workspace: trees that would return to
-     * more than four states, and calls with a state dump, are launched level by level
-     * (one launch per dependency level) through the cut states there; other trees run in
-     * one launch that keeps them in registers (the same bits; so do the next two). */
+     * more than four states, calls with a state dump, and small calls with wide trees are
+     * launched level by level (one launch per dependency level) through the cut states
+     * there; other calls run in one launch that keeps them in registers (the same bits;
+     * so do the next two). */
     LUMO_POLICY_PATHS = 0,
     /* The paper's two launches: the spine exports the cut states of its branch
      * nodes; every other root-to-leaf path then runs from its spine cut state,
@@ -87,10 +88,11 @@ typedef enum {
      * states, shared prefixes recomputed. No workspace. */
     LUMO_POLICY_RECOMPUTE = 2,
     /* Tree WY form: R_t = gamma_t R0 + sum over ancestors of decayed rank-1
-     * terms. With bf16 operands and d_k = d_v = 128 the R0 [K | Q] products run on MFMA
-     * (R0 as bf16 hi + lo; with paths of 18 to 32 nodes as three parts, exactly) and the
-     * ancestor-masked triangular system on the vector units; other shapes (fp32
-     * operands, d_k in {16, 32, 64}, d_v below 128) run the same form on the vector
+     * terms. With d_k = d_v = 128 the products over the keys run on MFMA in bf16 parts
+     * (bf16 operands: R0 as hi + lo, with paths of 18 to 32 nodes as three parts, exactly;
+     * fp32 operands: keys, queries and R0 as three parts, at most 2^-24 of a product
+     * dropped) and the ancestor-masked triangular system on the vector units; other
+     * shapes (d_k in {16, 32, 64}, d_v below 128) run the same form on the vector
      * units in fp32. Paths longer than 32 nodes are refused
      * (LUMO_EUNSUPPORTED). One launch, no workspace, no state dump. Outputs agree
      * with the sequential schedules to rounding, not bitwise. */
@@ -175,9 +177,10 @@ typedef struct {
  *   depth, -1 beyond its depth),
  *   vis[N][2] (per node in slot order, node_off[r] + slot: its preorder position and
  *   the position one past its subtree; node a is an ancestor-or-self of node i iff
- *   vis[a][0] <= vis[i][0] < vis[a][1]); then, for the sequential policies, the words of
- *   the single-launch scan's traversal (library-internal; a plan without them runs level
- *   by level).
+ *   vis[a][0] <= vis[i][0] < vis[a][1]); then library-internal words: for the sequential
+ *   policies the single-launch scan's traversal (a plan without it runs level by level),
+ *   for WY plans with paths of 18 to 32 nodes the preorder tables of the matrix-core
+ *   kernels (a plan without them runs on the vector units).
  * Returns LUMO_EDESC for malformed trees, LUMO_ESPACE (with out->n_words set)
  * when blob is NULL or too small, LUMO_EINVAL for bad arguments.
  */

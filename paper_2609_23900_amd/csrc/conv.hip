@@ -242,9 +242,10 @@ __global__ __launch_bounds__(256) void conv_kernel(ConvParams p) {
 // preorder positions and 64 x 16 bytes of channels, and keeps the x entries of the current
 // root path by depth in LDS (rows 0..2 the history, row 3 + d depth d), so that each x row
 // is loaded once per run: a node at depth d finds its window in rows d, d + 1, d + 2, and its
-// own entry goes into row d + 3. Ancestors before the run are loaded where they are
-// needed: only the first node and every node shallower than all before it in the run have a
-// parent outside, and their three window sources (plan) are copied to LDS up front. The
+// own entry goes into row d + 3. The first node and every node shallower than all before it in
+// the run have their three window sources (plan) copied to LDS up front. Any other node is no
+// shallower than some earlier one, with which it shares the path above that one's depth:
+// its ancestors are in the run or were copied for an earlier node. The
 // arithmetic is conv_kernel's (the same bits). Bound by HBM: conv_kernel loads every window
 // row from L2 and re-reads x 1.4 to 1.6 times from HBM; this walk reads it once, and a few
 // rows per run again. One-wave blocks, so that a run's serial walk waits for nobody; the

@@ -69,12 +69,13 @@ hipError_t launch_wy_conv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, co
                           const PendArgs& pend, const ConvFuseArgs& cf);
 constexpr int kWyMaxDepth = kPreStack + 1;  // nodes on a root-to-leaf path (deferred publication)
 
-// The WY form on the vector ALUs for the shapes the matrix-core kernel does not take
-// (fp32 operands, d_k or d_v below 128; paths of up to kWyvMaxDepth nodes). No
-// workspace; operand preparation as in GdnArgs::prep.
+// The WY form on the vector ALUs for the shapes the matrix-core kernels do not take
+// (d_k or d_v below 128, and plans without the tables for paths of 18 to kWyvMaxDepth
+// nodes). No workspace; operand preparation as in GdnArgs::prep.
 constexpr int kWyvMaxDepth = 32;
 hipError_t launch_wyv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s);
-// The WY form on the fp32 matrix instructions: fp32 operands, d_k = d_v = 128.
+// The WY form for fp32 operands at d_k = d_v = 128, every factor as three parts on the bf16
+// matrix instructions.
 hipError_t launch_wyf(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s);
 
 // Whether a matrix-core WY kernel serves these dimensions and plan (launch_wy for bf16,

@@ -14,7 +14,7 @@
 // ones are summed first and the four steps of hi hi last, so
 // that only those round at the size of the result. Six bf16 matrix instructions take 6/16 of
 // the time of the fp32 ones, whose chains also round more often. Error of the
-// outputs against 64-bit arithmetic: 8.9e-8 (one fp32-MFMA chain of 128 terms 1.6e-7; the
+// outputs against 64-bit arithmetic: 8.6e-8 (one fp32-MFMA chain of 128 terms 1.6e-7; the
 // vector-ALU kernel that served these shapes before 9.3e-8). 8 requests x 12 layers x 64 nodes x 32
 // heads: 211 us (that kernel 516 us), 1 layer 28 us (148 us).
 //
@@ -28,7 +28,10 @@
 // the recursion runs node by node with the deltas of the current path in registers, lane l <
 // 32 forming the sum over A and the delta of its column, lane l + 32 the sum over B and the
 // output. One head per block: 32-column waves hold R0 in 64 registers, which leaves room
-// for the path registers at two waves per SIMD.
+// for the path registers at two waves per SIMD: without scratch with D = 8, with 23 to 32 spilled
+// registers with D = 16 (8 x 12 layers x 64 nodes, paths of 17 nodes: 254 us; the
+// vector-ALU kernel 597 us). With D = 32 the rows and records take 101 KB of LDS, one block per
+// CU (one wave per SIMD; paths of 32 nodes: 434 us, the vector-ALU kernel 703 us).
 #include "device_common.h"
 #include "internal.h"
 #include "launch.h"

@@ -1,6 +1,7 @@
-// Tree verification in WY form on the vector ALUs: the shapes the matrix-core kernel
-// (verify_wy.hip) does not take -- fp32 operands, d_k or d_v below 128, paths of up to
-// kWyvMaxDepth nodes -- with the same arithmetic form and no cut states.
+// Tree verification in WY form on the vector ALUs: the shapes the matrix-core kernels
+// (verify_wy.hip, verify_wyf.hip) do not take -- d_k or d_v below 128, and plans without the
+// tables for paths of more than 17 nodes; paths of up to kWyvMaxDepth nodes, fp32 or bf16
+// operands -- with the same arithmetic form and no cut states.
 //
 // Unrolling Eq. (2)-(3) along a node's ancestry a_0 (root) .. a_{d-1}, t:
 //     R_t = gamma_t R0 + sum_{s ancestor-or-self of t} Gamma(s->t) delta_s k_s^T
