@@ -9,10 +9,11 @@
 //                     path with the same row update the verifier uses, store in place;
 //                     the path's key rows, gates and value entries are staged in LDS
 //                     while the state loads are in flight. Two forms with the same bits
-//                     (tiles of 16 columns, and of 64 for large state banks). Skipped
+//                     (tiles of 16 columns, and of 64 for large grids). Skipped
 //                     when the state is NULL (publication deferred).
 // Empty or invalid paths leave the state and the history untouched.
 #include "device_common.h"
+#include "dispatch.h"
 #include "internal.h"
 #include "commit.h"
 
@@ -192,7 +193,7 @@ __global__ __launch_bounds__(256, 4) void replay_kernel(ReplayParams p, const ty
 }
 
 // The same replay with 64 value columns per wavefront, one per lane, for state banks beyond
-// the Infinity Cache (launch_replay_dk). The same bits: gdn_row_update's order.
+// the Infinity Cache and large grids of short keys (replay_narrow). The same bits: gdn_row_update's order.
 // Path entries whose key row, row, decay, beta and value are fetched before the loop.
 constexpr int kPrefetch = 16;
 
@@ -458,15 +459,10 @@ __global__ __launch_bounds__(256) void path_hist_layers_kernel(PathParams pp, Hi
 }
 
 template <int DK, int OPT>
-void launch_replay_dk(const lumo_gdn_dims& d, hipStream_t s, ReplayParams& p, const CommitArgs& a) {
+void launch_replay_dk(const lumo_gdn_dims& d, bool narrow, hipStream_t s, ReplayParams& p, const CommitArgs& a) {
     using T = typename Op<OPT>::T;
     const long heads = (long)d.n_req * d.n_layers * d.h_v;
-    // 16-column wavefronts keep twice as much of the state in flight, and win while the state
-    // bank stays in the 256 MB Infinity Cache between calls (8 requests x 32 heads, d =
-    // 128, bf16: 6 layers 53.8 -> 41.7 us, 12 layers 85.6 -> 72.8 us; fp32 12 layers 103 -> 75
-    // us). Beyond it the 64-column form, which reads whole 256-byte rows, is as fast or
-    // faster (18 layers 122 against 136 us, 48 layers 334 against 339 us).
-    if (heads * DK * d.d_v * (long)sizeof(float) <= (256l << 20)) {
+    if (narrow) {
         p.n_ct = d.d_v / 16;
         p.nwk = p.group * p.n_ct;
         p.n_wb = (p.nwk + 3) / 4;
@@ -482,12 +478,12 @@ void launch_replay_dk(const lumo_gdn_dims& d, hipStream_t s, ReplayParams& p, co
 }
 
 template <int OPT>
-hipError_t launch_replay(const lumo_gdn_dims& d, hipStream_t s, ReplayParams& p, const CommitArgs& a) {
+hipError_t launch_replay(const lumo_gdn_dims& d, bool narrow, hipStream_t s, ReplayParams& p, const CommitArgs& a) {
     switch (d.d_k) {
-        case 16: launch_replay_dk<16, OPT>(d, s, p, a); break;
-        case 32: launch_replay_dk<32, OPT>(d, s, p, a); break;
-        case 64: launch_replay_dk<64, OPT>(d, s, p, a); break;
-        default: launch_replay_dk<128, OPT>(d, s, p, a); break;
+        case 16: launch_replay_dk<16, OPT>(d, narrow, s, p, a); break;
+        case 32: launch_replay_dk<32, OPT>(d, narrow, s, p, a); break;
+        case 64: launch_replay_dk<64, OPT>(d, narrow, s, p, a); break;
+        default: launch_replay_dk<128, OPT>(d, narrow, s, p, a); break;
     }
     return hipGetLastError();
 }
@@ -535,7 +531,8 @@ hipError_t launch_commit(const lumo_gdn_dims& d, const lumo_tree_desc& desc, con
     rp.d_v = d.d_v;
     rp.group = d.h_v / d.h_k;
     rp.prep = a.prep;
-    e = d.op_dtype == LUMO_BF16 ? launch_replay<1>(d, s, rp, a) : launch_replay<0>(d, s, rp, a);
+    const bool narrow = replay_narrow(d, pl, a.max_path);
+    e = d.op_dtype == LUMO_BF16 ? launch_replay<1>(d, narrow, s, rp, a) : launch_replay<0>(d, narrow, s, rp, a);
     if (e != hipSuccess) return e;
     }
 

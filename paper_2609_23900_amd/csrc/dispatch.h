@@ -40,6 +40,30 @@ inline bool scan_tree_faster(const lumo_gdn_dims& d, const lumo_plan& p, const i
     return level >= tree;
 }
 
+// Whether the commit's replay (commit.hip) takes wavefronts of 16 value columns rather than 64.
+// Both are bound by the state bank's way through HBM or the Infinity Cache; 16 columns keep
+// more of it in flight and shorten each path step, 64 read whole rows and share each key row.
+// So 16 while the bank stays in the 256 MB cache between calls, and for heads that leave
+// columns of a 64-wide tile idle (d = 128 x 16, 768 heads, 8 steps: 20.0 -> 10.0 us); with d_k =
+// 128 at every such size (8 steps, bf16: 32 heads 18.5 -> 10.0, 512 25.3 -> 20.5, 3,072
+// 86.4 -> 72.8 us), with shorter keys, whose steps are short already, up to 1,024 tiles of 64
+// columns, one wave per SIMD, and 1,536 in bf16 (bf16 d = 64 x 128, 8 steps: 512 heads 16.5 ->
+// 14.2 us, 768 18.3 -> 17.7, 2,048 33.0 -> 39.4; fp32 d = 32 x 128: 256 heads 9.4 -> 8.3 us, 768 11.7
+// -> 12.3, 2,048 21.6 -> 26.0, 12,288 88 -> 109). Steps are few where the trees or max_path are
+// short: up to three steps, 512 of these tiles (bf16, d = 128 x 128, 512 heads: one step 14.3
+// against 17.2 us, two 1.12 times, four as long), except where a step converts nothing
+// (fp32, d_k = 128: 0.89 to 1.04 times).
+// Beyond 256 MB: bf16, d = 128, 18 layers x 8 requests x 32 heads 122 against 136 us.
+inline bool replay_narrow(const lumo_gdn_dims& d, const lumo_plan& p, int max_path) {
+    const int64_t heads = (int64_t)d.n_req * d.n_layers * d.h_v;
+    const int64_t tiles = heads * ((d.d_v + 63) / 64);
+    if (heads * d.d_k * d.d_v * (int64_t)sizeof(float) > (int64_t(256) << 20)) return false;
+    const bool few = std::min(max_path, (int)p.max_depth) <= 3;
+    if (d.d_v <= 32) return !few || d.d_k > 32 || tiles <= 1024;
+    if (d.d_k == 128) return !few || d.op_dtype == LUMO_F32 || tiles <= 512;
+    return tiles <= (few ? 512 : d.op_dtype == LUMO_F32 ? 1024 : 1536);
+}
+
 // The conv's walk over runs (conv.hip): nodes per run and channels per lane, 0 nodes where the
 // run kernel is faster. A run starts by loading its ancestors and weights, and the grid has
 // as many runs for every request as the largest one needs. So the walk takes calls

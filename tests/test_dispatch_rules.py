@@ -26,6 +26,9 @@ extern "C" int scan_tree(const lumo_gdn_dims* d, const lumo_plan* p, const int32
 extern "C" int conv_run(const lumo_gdn_dims* d, const lumo_plan* p, const int32_t* b, int channels) {
     return lumo::conv_walk(*d, *p, b, channels).run_nodes;
 }
+extern "C" int replay(const lumo_gdn_dims* d, const lumo_plan* p, int max_path) {
+    return lumo::replay_narrow(*d, *p, max_path);
+}
 ''')
     lib = d / "rules.so"
     subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-I", os.path.join(ROOT, "include"), "-I",
@@ -116,3 +119,32 @@ def test_conv_walk_refuses_long_paths(rules):
     plan, blob = _plan([trees.chain(18)] * 64, "recompute")
     d = L.dims(64, 48, 1, 1, 128, 128, L.LUMO_F32)
     assert rules.conv_run(ctypes.byref(d), ctypes.byref(plan), L._hptr(blob), 8192) == 0
+
+
+@pytest.mark.parametrize("heads,d_k,d_v,bf16,depth,max_path,narrow", [
+    # measured with 64 and with 16 columns, us
+    ((1, 1, 32), 128, 128, True, 32, 32, 1),      # 8 steps 18.5, 10.0
+    ((64, 1, 32), 128, 128, True, 32, 32, 1),     # 63.7, 54.0
+    ((64, 1, 32), 64, 128, True, 32, 32, 0),      # 33.0, 39.4
+    ((16, 1, 32), 64, 128, True, 32, 32, 1),      # 16.5, 14.2
+    ((16, 1, 48), 64, 128, True, 32, 32, 1),      # 18.4, 18.4; 32 steps 46, 36
+    ((16, 1, 48), 64, 128, False, 32, 32, 0),     # 16.9, 18.5
+    ((64, 4, 32), 64, 128, False, 32, 32, 0),     # 101, 141: at the 256 MB
+    ((64, 1, 32), 32, 128, False, 32, 32, 0),     # 21.6, 26.0
+    ((64, 4, 48), 32, 128, False, 32, 32, 0),     # 88, 109
+    ((16, 1, 32), 64, 64, False, 32, 32, 1),      # 12.9, 10.3
+    ((64, 1, 32), 64, 64, False, 32, 32, 0),      # 23.5, 24.4
+    ((64, 4, 48), 128, 16, True, 32, 32, 1),      # 115, 52
+    ((64, 4, 32), 16, 16, False, 32, 32, 1),      # 17.7, 15.4
+    ((16, 1, 32), 128, 128, True, 1, 16, 0),      # one step 14.3, 17.2
+    ((16, 1, 32), 128, 128, True, 16, 2, 0),      # two steps, 1.12 times
+    ((16, 1, 32), 128, 128, True, 16, 4, 1),      # four steps, 0.99 times
+    ((64, 1, 32), 128, 128, False, 1, 16, 1),     # 51.3, 48.0
+    ((4, 1, 32), 128, 128, True, 1, 16, 1),       # 9.2, 8.4
+    ((18, 8, 32), 128, 128, True, 32, 32, 0),     # beyond the cache: 122, 136
+])
+def test_replay_form_is_the_faster_one(rules, heads, d_k, d_v, bf16, depth, max_path, narrow):
+    n_req, layers, h_v = heads
+    plan, _ = _plan([trees.chain(depth)] * n_req, "recompute")
+    d = L.dims(n_req, layers, 1, h_v, d_k, d_v, L.LUMO_BF16 if bf16 else L.LUMO_F32)
+    assert rules.replay(ctypes.byref(d), ctypes.byref(plan), max_path) == narrow
