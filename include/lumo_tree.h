@@ -92,8 +92,9 @@ typedef enum {
      * (bf16 operands: R0 as hi + lo, with paths of 18 to 32 nodes as three parts, exactly;
      * fp32 operands: keys, queries and R0 as three parts, at most 2^-24 of a product
      * dropped) and the ancestor-masked triangular system on the vector units; other
-     * shapes (d_k in {16, 32, 64}, d_v below 128) run the same form on the vector
-     * units in fp32. Paths longer than 32 nodes are refused
+     * shapes (d_k in {16, 32, 64}, d_v below 128), and fp32 operands or paths of 18 to
+     * 32 nodes in calls whose trees have a few nodes only, run the same form on the
+     * vector units in fp32. Paths longer than 32 nodes are refused
      * (LUMO_EUNSUPPORTED). One launch, no workspace, no state dump. Outputs agree
      * with the sequential schedules to rounding, not bitwise. */
     LUMO_POLICY_WY = 3

@@ -8,6 +8,7 @@
 
 #include "internal.h"
 #include "commit.h"
+#include "dispatch.h"
 #include "launch.h"
 #include "verify_wy.h"
 #include "select.h"
@@ -76,9 +77,9 @@ lumo_status check_wy(const lumo_gdn_dims* d, const lumo_tree_desc* desc, const c
     return LUMO_OK;
 }
 
-// A WY plan's verification: the matrix-core kernel for its shapes, the vector-ALU WY
+// A WY plan's verification: the matrix-core kernels for their shapes, the vector-ALU WY
 // kernel for the others (any supported d_k, d_v and operand type; paths of at most
-// kWyvMaxDepth nodes).
+// kWyvMaxDepth nodes) and for trees too small to fill a chunk (wy_vector_faster).
 lumo_status check_wy_verify(const lumo_gdn_dims* d, const lumo_tree_desc* desc, const char* fn) {
     if (desc->plan.policy != LUMO_POLICY_WY)
         return fail(LUMO_EUNSUPPORTED, "%s: needs a plan built for LUMO_POLICY_WY (plan policy %d)", fn,
@@ -90,7 +91,7 @@ lumo_status check_wy_verify(const lumo_gdn_dims* d, const lumo_tree_desc* desc, 
 }
 
 hipError_t launch_wy_any(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s) {
-    if (!wy_mfma_shape(d, desc)) return launch_wyv(d, desc, a, s);
+    if (!wy_mfma_shape(d, desc) || wy_vector_faster(d, desc.plan, desc.host_blob)) return launch_wyv(d, desc, a, s);
     return d.op_dtype == LUMO_BF16 ? launch_wy(d, desc, a, s) : launch_wyf(d, desc, a, s);
 }
 

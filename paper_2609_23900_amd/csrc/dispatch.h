@@ -40,6 +40,39 @@ inline bool scan_tree_faster(const lumo_gdn_dims& d, const lumo_plan& p, const i
     return level >= tree;
 }
 
+// Whether the WY form on the vector ALUs (verify_wyv.hip) is estimated to finish before the
+// matrix-core one, where both serve the plan: fp32 operands, and bf16 with paths of more than 17
+// nodes, at d = 128. The matrix-core kernels pay for whole chunks and half-chunks (16
+// nodes), the vector one node by node, so tiny trees are its own. Estimated are the work of all
+// heads and the largest tree's serial time; they overlap to four fifths with trees of one
+// size and hardly where one large tree is left at the end. Coefficients in microseconds, from
+// trees of 1 to 66 nodes, 8 to 8,192 heads. Matrix cores (vector ALUs): one node 32 heads 10.0
+// (5.4), 2,048 heads 47 (24); four nodes 32 heads 10.0 (11.5), 2,048 heads 47 (37); 9 nodes 47
+// (61). Chains of 18, 2,048 heads, 143 (117), of 24 134 (151). 8,192 heads, 63 requests of one
+// node beside one of 18: 363 (136), bf16 171 (137), beside one of 64 in 8 levels 194 (242).
+inline bool wy_vector_faster(const lumo_gdn_dims& d, const lumo_plan& p, const int32_t* host_blob) {
+    const bool f32 = d.op_dtype == LUMO_F32, deep = p.max_depth > kPreStack + 1;
+    if (!f32 && !deep) return false;
+    const float chunk = !f32 ? 0.0104f : deep ? 0.0235f : p.max_depth > 9 ? 0.02f : 0.0127f;  // a request's first
+    const float half = !f32 ? 0.0105f : deep ? 0.0215f : 0.01f;
+    const float depth = (float)p.max_depth;
+    int64_t requests = 0, halves = 0;
+    for (int r = 0; r < d.n_req; ++r) {
+        const int n = host_blob[p.o_node_off + r + 1] - host_blob[p.o_node_off + r];
+        requests += n > 0;
+        halves += (n + kPreChunk / 2 - 1) / (kPreChunk / 2);
+    }
+    const float apart = 0.8f - 0.6f * (float)p.total_nodes / (float)std::max<int64_t>(1, requests * p.max_nodes);
+    auto time = [&](float work, float serial) { return std::max(work, serial) + apart * std::min(work, serial); };
+    const float heads = (float)d.n_layers * (float)d.h_v;
+    const float vector = time(heads * (0.0085f * (float)requests + (0.0022f + 3e-5f * depth) * (float)p.total_nodes),
+                              3.f + (float)p.max_nodes * (2.1f + 0.025f * depth));
+    const float matrix = time(heads * (chunk * (float)requests + 0.01f * (float)(p.n_chunks - requests) + half * (float)halves),
+                              (deep ? 17.f : p.max_depth > 9 ? 12.f : 10.f) +
+                                  8.5f * (float)((p.max_nodes + kPreChunk - 1) / kPreChunk - 1));
+    return vector < matrix;
+}
+
 // Whether the commit's replay (commit.hip) takes wavefronts of 16 value columns rather than 64.
 // Both are bound by the state bank's way through HBM or the Infinity Cache; 16 columns keep
 // more of it in flight and shorten each path step, 64 read whole rows and share each key row.

@@ -71,7 +71,7 @@ constexpr int kWyMaxDepth = kPreStack + 1;  // nodes on a root-to-leaf path (def
 
 // The WY form on the vector ALUs for the shapes the matrix-core kernels do not take
 // (d_k or d_v below 128, and plans without the tables for paths of 18 to kWyvMaxDepth
-// nodes). No workspace; operand preparation as in GdnArgs::prep.
+// nodes) and for trees of a few nodes (wy_vector_faster). No workspace; operand preparation as in GdnArgs::prep.
 constexpr int kWyvMaxDepth = 32;
 hipError_t launch_wyv(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, hipStream_t s);
 // The WY form for fp32 operands at d_k = d_v = 128, every factor as three parts on the bf16

@@ -1,7 +1,9 @@
 // Tree verification in WY form on the vector ALUs: the shapes the matrix-core kernels
 // (verify_wy.hip, verify_wyf.hip) do not take -- d_k or d_v below 128, and plans without the
 // tables for paths of more than 17 nodes; paths of up to kWyvMaxDepth nodes, fp32 or bf16
-// operands -- with the same arithmetic form and no cut states.
+// operands -- and calls whose trees are too small to fill the chunks of verify_wyf.hip or of the
+// deep form of verify_wy.hip (wy_vector_faster in dispatch.h). The same arithmetic form, no cut
+// states.
 //
 // Unrolling Eq. (2)-(3) along a node's ancestry a_0 (root) .. a_{d-1}, t:
 //     R_t = gamma_t R0 + sum_{s ancestor-or-self of t} Gamma(s->t) delta_s k_s^T

@@ -26,6 +26,9 @@ extern "C" int scan_tree(const lumo_gdn_dims* d, const lumo_plan* p, const int32
 extern "C" int conv_run(const lumo_gdn_dims* d, const lumo_plan* p, const int32_t* b, int channels) {
     return lumo::conv_walk(*d, *p, b, channels).run_nodes;
 }
+extern "C" int wy_vector(const lumo_gdn_dims* d, const lumo_plan* p, const int32_t* b) {
+    return lumo::wy_vector_faster(*d, *p, b);
+}
 extern "C" int replay(const lumo_gdn_dims* d, const lumo_plan* p, int max_path) {
     return lumo::replay_narrow(*d, *p, max_path);
 }
@@ -148,3 +151,40 @@ def test_replay_form_is_the_faster_one(rules, heads, d_k, d_v, bf16, depth, max_
     plan, _ = _plan([trees.chain(depth)] * n_req, "recompute")
     d = L.dims(n_req, layers, 1, h_v, d_k, d_v, L.LUMO_BF16 if bf16 else L.LUMO_F32)
     assert rules.replay(ctypes.byref(d), ctypes.byref(plan), max_path) == narrow
+
+
+def _deep(n, depth):
+    """A chain of `depth` nodes, the others under the root."""
+    return np.array(list(range(-1, depth - 1)) + [0] * (n - depth), np.int32)
+
+
+@pytest.mark.parametrize("sizes,layers,h_v,bf16,vector", [
+    # (nodes, levels) per request; measured on the matrix cores and on the vector ALUs, us
+    ([(1, 1)], 1, 32, False, 1),                          # 10.0, 5.4
+    ([(3, 3)] * 4, 1, 32, False, 1),                      # 10.0, 9.5
+    ([(4, 4)], 1, 32, False, 0),                          # 10.0, 11.5
+    ([(4, 4)] * 64, 1, 32, False, 1),                     # 47, 37
+    ([(1, 1)] * 64, 4, 32, False, 1),                     # 185, 97
+    ([(7, 7)] * 64, 1, 32, False, 0),                     # 47, 51
+    ([(8, 4)] * 64, 4, 32, False, 0),
+    ([(12, 12)] * 64, 1, 32, False, 0),                   # 60, 78
+    ([(18, 18)] * 64, 1, 32, False, 1),                   # 141, 115
+    ([(18, 18)] * 16, 1, 32, False, 0),                   # 38, 52
+    ([(24, 24)] * 64, 1, 32, False, 0),                   # 134, 151
+    ([(64, 8)] * 8, 12, 32, False, 0),
+    ([(64, 18)] * 64, 4, 32, False, 0),
+    ([(1, 1)] * 63 + [(18, 18)], 4, 32, False, 1),        # 363, 136
+    ([(1, 1)] * 63 + [(64, 20)], 4, 32, False, 1),        # 378, 268
+    ([(1, 1)] * 63 + [(64, 20)], 1, 32, False, 0),
+    ([(1, 1)] * 63 + [(64, 8)], 4, 32, False, 0),         # 194, 242
+    ([(4, 4)] * 63 + [(18, 18)], 4, 32, True, 0),         # 172, 188
+    ([(0, 0)] * 63 + [(1, 1)], 1, 32, False, 1),
+    ([(1, 1)] * 63 + [(18, 18)], 4, 32, True, 1),         # 171, 137
+    ([(18, 18)] * 64, 4, 32, True, 0),
+    ([(96, 32)] * 16, 4, 32, True, 0),
+    ([(1, 1)] * 64, 4, 32, True, 0),                      # paths of up to 17 nodes: always the matrix cores
+])
+def test_wy_form_is_the_faster_one(rules, sizes, layers, h_v, bf16, vector):
+    plan, blob = _plan([_deep(*s) if s[0] else np.zeros(0, np.int32) for s in sizes], "wy")
+    d = L.dims(len(sizes), layers, 1, h_v, 128, 128, L.LUMO_BF16 if bf16 else L.LUMO_F32)
+    assert rules.wy_vector(ctypes.byref(d), ctypes.byref(plan), L._hptr(blob)) == vector

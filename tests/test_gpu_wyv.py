@@ -1,7 +1,8 @@
 """The vector-ALU WY kernel on the shapes it serves: heads below 128 in either dimension, with
-paths up to its limit of 32 nodes and operands prepared in the kernel; and d = 128 beyond 17
-nodes per path with a plan that lacks the tables of the matrix-core forms. Also plans
-without the optional words of the sequential policies, which run level by level.
+paths up to its limit of 32 nodes and operands prepared in the kernel; fp32 trees of up to three
+nodes at d = 128; and d = 128 beyond 17 nodes per path with a plan that lacks the tables of the
+matrix-core forms. Also plans without the optional words of the sequential policies, which run
+level by level.
 
 Every node against the fp64 oracle under the parity tolerances."""
 from __future__ import annotations
@@ -28,6 +29,8 @@ QKN, RAWG = L.LUMO_PREP_QK_NORM, L.LUMO_PREP_RAW_GATES
 
 def _trees(case):
     rng = np.random.default_rng(81)
+    if case == "tiny":  # too small for a chunk of the matrix-core form
+        return [trees.chain(1), np.zeros(0, np.int32), trees.chain(2), trees.chain(3), np.array([-1, 0, 0], np.int32)]
     if case == "deep":
         return [trees.chain(18), trees.chain(31), trees.chain(32), trees.random_tree(rng, 60, 25, trees.bmax_uniform(2)),
                 np.zeros(0, np.int32)]
@@ -79,6 +82,15 @@ def test_vector_alu_wy(case, d_k, d_v, op_dtype, flags):
     print(f"[gpu] wyv {case} d={d_k}x{d_v} dtype={op_dtype} prep={flags}", flush=True)
     wl, st, oprep = _setup(case, d_k, d_v, op_dtype, flags)
     _check(wl, st, oprep)
+
+
+@pytest.mark.parametrize("flags,h_k,h_v", [(0, 2, 4), (QKN | RAWG, 2, 4), (QKN, 16, 48)])
+def test_vector_alu_wy_of_tiny_trees(flags, h_k, h_v):
+    print(f"[gpu] wyv tiny trees d=128 fp32 heads={h_k}/{h_v} prep={flags}", flush=True)
+    wl, st, oprep = _setup("tiny", 128, 128, ops.F32, flags, h_k, h_v)
+    o = _check(wl, st, oprep)
+    rows = set(oracle.plan.flat_rows(wl.parents, wl.row_off).tolist())
+    assert np.all(o[:, [x for x in range(wl.total_rows) if x not in rows]] == 0)
 
 
 @pytest.mark.parametrize("op_dtype,flags", [(ops.F32, 0), (ops.BF16, 0), (ops.F32, QKN | RAWG), (ops.BF16, QKN)])
