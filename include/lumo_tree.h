@@ -75,9 +75,9 @@ typedef enum {
     /* Dependent path groups: the tree is cut into disjoint first-child chains; a
      * chain starts from the pre-tree state (the spine) or from the cut state of its
      * parent; each node is updated once. Needs a workspace: trees that would return to
-     * more than four states, calls with a state dump, and small calls with wide trees are
-     * launched level by level (one launch per dependency level) through the cut states
-     * there; other calls run in one launch that keeps them in registers (the same bits;
+     * more than four states, calls with a state dump, trees of a few nodes and small calls
+     * with wide trees are launched level by level (one launch per dependency level) through
+     * the cut states there; other calls run in one launch that keeps them in registers (the same bits;
      * so do the next two). */
     LUMO_POLICY_PATHS = 0,
     /* The paper's two launches: the spine exports the cut states of its branch

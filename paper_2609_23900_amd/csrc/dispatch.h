@@ -12,30 +12,45 @@ namespace lumo {
 
 // Whether the single-launch scan (verify_scan.hip) is estimated to finish before the level-by-level
 // one. It walks a tree's nodes one after the other, whatever their shape; the other form
-// takes the longest segment of each level, and its launches, waves and cut states add up. Calls
-// of more than 1,024 column tiles (four requests x 32 heads at d_v = 128) are bound by that
-// work and always ran faster in the single launch. Below, the coefficients (microseconds;
-// per launch, node of a longest segment, and thousand waves, node updates and cut tiles) are
-// fitted to both forms over 236 calls of 1 to 32 requests, PATHS, TWO_LEVEL and
-// RECOMPUTE, d_k = 16 to 128: 64-node trees to stars of 256 nodes. The choice is at most 5%
-// behind the better form in each. One request, one layer, 32 heads, d = 128: 256 leaves under a
-// root 48 us by level, 143 us in one launch; 256 nodes of 8 levels, TWO_LEVEL 109 and 143
-// us, PATHS 178 and 143 us; 64 nodes of 8 levels, PATHS 99 and 39 us.
+// takes the longest segment of each level, and its launches, waves and cut states add up. Both
+// estimates in microseconds, linear in the plan: a node walked or a step of a longest segment,
+// and per thousand column tiles (16 columns there, 64 here) a request's or segment's state, a node
+// and a cut state. Coefficients are fitted per key length to both forms, apart for calls of
+// more and of less than 1,024 16-column tiles (the device full or not), over 7,575 calls of 1
+// to 64 requests, chains, stars and trees of 2 to 20 levels with 1 to 256 nodes under PATHS,
+// TWO_LEVEL and RECOMPUTE. Of these the choice is more than 5% behind the better form in 48 (at
+// most 32%), and more than 5% behind the level-by-level form in 29. One layer, 32 heads, d = 128,
+// level by level and in one launch: one request, 256 leaves under a root 48 and 143 us; 256
+// nodes of 8 levels, TWO_LEVEL 109 and 143 us, PATHS 178 and 143 us; 64 nodes of 8 levels,
+// PATHS 99 and 39 us; 64 requests of one node 24 and 32 us, of 8 in a chain 67 and 58 us.
+struct ScanCost {
+    float tree, tree_node, tree_state, tree_work;                // single launch
+    float level, level_step, level_state, level_work, level_cut;  // level by level
+};
 inline bool scan_tree_faster(const lumo_gdn_dims& d, const lumo_plan& p, const int32_t* host_blob) {
-    if ((int64_t)d.n_req * d.n_layers * d.h_v * (d.d_v / 16) > 1024) return true;
-    const float s = (float)d.d_k / 128.f;
-    const float kilo = (float)(d.n_layers * d.h_v * ((d.d_v + 63) / 64)) * 1e-3f;  // waves per segment
-    const float node = d.d_k == 128 ? 0.56f : d.d_k == 64 ? 0.37f : d.d_k == 32 ? 0.48f : 0.21f;
-    const float tree = 4.f + node * (float)p.max_nodes;
-    float level = (2.5f + 5.f * s) * (float)p.n_levels + kilo * (0.9f * s * (float)p.n_seg + (0.06f + 0.7f * s) * (float)p.n_seg_nodes +
-                                                                 5.f * s * (float)p.n_cuts);
-    const float step = 0.4f + 1.6f * s;
-    if (level + step * (float)p.max_seg_len >= tree) return true;
+    // key lengths of 16, 32, 64 and 128
+    static const ScanCost small[4] = {{2.374f, 0.236f, 1.432f, 0.085f, 2.275f, 0.645f, 0.641f, 0.061f, 0.736f},
+                                      {3.260f, 0.470f, 0.013f, 0.012f, 2.678f, 0.815f, 0.108f, 0.232f, 1.834f},
+                                      {3.333f, 0.338f, 0.245f, 0.021f, 3.231f, 0.935f, 0.242f, 0.389f, 11.231f},
+                                      {4.712f, 0.463f, 0.684f, 0.025f, 4.422f, 1.639f, 0.529f, 0.763f, 20.296f}};
+    static const ScanCost large[4] = {{1.801f, 0.191f, 0.913f, 0.031f, 1.734f, 0.705f, 0.210f, 0.219f, 1.223f},
+                                      {3.736f, 0.525f, 0.558f, 0.037f, 1.567f, 0.946f, 0.481f, 0.262f, 2.235f},
+                                      {1.884f, 0.196f, 1.142f, 0.089f, 2.340f, 1.010f, 0.332f, 0.720f, 5.153f},
+                                      {2.107f, 0.286f, 1.658f, 0.194f, 2.461f, 2.576f, 1.058f, 1.278f, 8.610f}};
+    const float heads = (float)d.n_layers * (float)d.h_v * 1e-3f;
+    const float narrow = heads * (float)(d.d_v / 16), wide = heads * (float)((d.d_v + 63) / 64);
+    const int key = d.d_k == 16 ? 0 : d.d_k == 32 ? 1 : d.d_k == 64 ? 2 : 3;
+    const ScanCost& c = (narrow * (float)d.n_req > 1.024f ? large : small)[key];
+    const float tree = c.tree + c.tree_node * (float)p.max_nodes +
+                       narrow * (c.tree_state * (float)d.n_req + c.tree_work * (float)p.total_nodes);
+    float level = c.level * (float)p.n_levels + wide * (c.level_state * (float)p.n_seg + c.level_work * (float)p.n_seg_nodes +
+                                                        c.level_cut * (float)p.n_cuts);
+    if (level + c.level_step * (float)p.max_seg_len >= tree) return true;
     for (int lv = 0; lv < p.n_levels; ++lv) {
         int longest = 0;
         for (int i = host_blob[p.o_level_off + lv]; i < host_blob[p.o_level_off + lv + 1]; ++i)
             longest = std::max(longest, (int)host_blob[p.o_seg + kSegWords * (int64_t)i + 3]);
-        level += step * (float)longest;
+        level += c.level_step * (float)longest;
     }
     return level >= tree;
 }

@@ -322,7 +322,7 @@ hipError_t launch_tree(int dk, const ScanTreeParams& p, long nb, hipStream_t s, 
 // Whether scan_tree_kernel takes a call: plans that carry the traversal and need at most
 // kScanSlots saved states, without node-state dump or operand preparation, where it is the
 // faster form (8 requests x 6 layers x 64 nodes, 32 heads, d = 128: 1,175 -> 280 us; small
-// calls with wide trees are not: scan_tree_faster).
+// calls with wide trees, and trees of a few nodes, are not: scan_tree_faster).
 bool scan_tree_takes(const lumo_gdn_dims& d, const lumo_tree_desc& desc, const GdnArgs& a, int64_t section) {
     if (section < 0 || desc.host_blob[section] > kScanSlots || a.node_states || a.prep.flags != 0) return false;
     return scan_tree_faster(d, desc.plan, desc.host_blob);

@@ -72,6 +72,15 @@ ONE = (1, 16, 32, 128, 128)  # one layer of 16 key and 32 value heads
     ("paths", _star(256), 8, ONE, 1),              # 269, 167
     ("two_level", _levels(64, 8), 8, (2, 8, 8, 128, 16), 1),   # 43, 37
     ("two_level", _star(100), 64, (1, 16, 32, 64, 64), 1),     # beyond 1,024 column tiles
+    ("paths", trees.chain(1), 64, (4, 16, 32, 128, 128), 0),   # 97, 154
+    ("recompute", trees.chain(3), 64, (4, 16, 32, 128, 128), 0),   # 123, 179
+    ("paths", trees.chain(16), 64, (4, 16, 32, 128, 128), 1),  # 427, 362
+    ("paths", trees.chain(1), 64, (1, 8, 16, 64, 128), 0),     # 6.4, 10.9
+    ("paths", trees.chain(2), 64, (4, 8, 8, 32, 128), 0),      # 8.7, 16.3
+    ("recompute", trees.chain(8), 64, (4, 8, 16, 128, 16), 1),     # 63, 30
+    ("recompute", _star(16), 1, ONE, 0),           # 7.6, 12.3
+    ("paths", _star(33), 2, (1, 8, 16, 128, 16), 0),           # 14.9, 21.4
+    ("paths", _levels(64, 8), 8, (6, 16, 32, 128, 128), 1),    # 1,175, 280
 ])
 def test_scan_form_is_the_faster_one(rules, policy, tree, n_req, shape, single):
     plan, blob = _plan([tree] * n_req, policy)

@@ -1,8 +1,9 @@
 """The sequential policies' single-launch scan against the level-by-level scan, bit for bit.
 
 A call that asks for the node states runs level by level; the same call without them
-takes the single launch (the layers are chosen so that it does at any tree: more than 1,024
-column tiles, below which calls with wide trees stay level by level). Both must leave the same output bits at every node row and touch
+takes the single launch (the layers are chosen so that it does: more than 1,024 column
+tiles, below which calls with wide trees stay level by level; only RECOMPUTE of the complete tree
+at d_k = 32 is level by level both times). Both must leave the same output bits at every node row and touch
 no pad row, for every key and value dimension, both operand types, grouped heads, trees that
 end on and around the 16-node chunks, zero to four saved states, and trees that need more
 (which stay level by level).
