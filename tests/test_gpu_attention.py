@@ -160,6 +160,7 @@ def test_tree_attention_paper_geometry_long_context():
     (4, 2, (33, 64), (1024, 1023), 40),    # more ranges allowed than tiles; ragged last tile
     (8, 1, (17, 2, 16), (900, 0, 1100), 9),    # 136 rows: the last chunk one row tile
     (8, 1, (16, 130), (63, 130), 300),     # short contexts keep one row tile per wave
+    (8, 8, (128, 5), (2000, 300), 9),      # several ranges of more than 1,024 (row, head) pairs
 ])
 def test_tree_attention_row_and_range_edges(h_q, h_kv, nodes, n_ctx, n_split):
     """Edges of the row chunks (16 and 32 rows per wave, 64 and 128 per block), of the key
